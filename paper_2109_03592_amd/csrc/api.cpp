@@ -1507,12 +1507,18 @@ sem_status sem_precond_apply(sem_mesh *m, const double *r, double *z, void *stre
         if (!m || !r || !z) fail(SEM_EINVAL, "sem_precond_apply: null argument");
         if (r == z) fail(SEM_EINVAL, "sem_precond_apply: r and z must be distinct");
         hipStream_t s = (hipStream_t)stream;
-        if (m->schwarz) schwarz_apply(m, r, z, nullptr, nullptr, s);
-        else launch_jacobi(m->h.nL, m->inv64, r, z, s);
-        if (m->coarse) {
+        if (m->schwarz) {
+            // the local solves also take the coarse term's element sums of r,
+            // and their sum into z adds its prolongation
+            schwarz_solves(m, r, nullptr, m->coarse != nullptr, nullptr, s);
+            if (m->coarse) coarse_solve(m, nullptr, nullptr, s);
+            schwarz_assemble(m, z, m->coarse != nullptr, nullptr, s);
+        } else if (m->coarse) {
             coarse_restrict<double>(m, r, m->inv64, s);
             coarse_solve(m, nullptr, nullptr, s);
-            coarse_prolong_add(m, z, s);
+            coarse_jacobi_prolong(m, r, z, s);
+        } else {
+            launch_jacobi(m->h.nL, m->inv64, r, z, s);
         }
         return SEM_OK;
     });

@@ -278,7 +278,7 @@ static void slot_coarse(sem_batch *B, int id, hipStream_t s, bool at_start = fal
     else coarse_restrict_w<float>(m, h.cw, static_cast<const float *>(d.r[1]), m->inv32, s);
     const int pairs = coarse_solve_w(m, h.cw, h.cw.dot, at_start ? nullptr : d.st + p, s);
     SEM_HIP(launch_reduce_scalar(h.cw.dot, 2 * (int64_t)pairs, h.cw.rz, s));
-    if (p == 0) coarse_prolong_w(m, h.cw, static_cast<double *>(const_cast<void *>(d.zc)), false, s);
+    if (p == 0) coarse_prolong_w(m, h.cw, static_cast<double *>(const_cast<void *>(d.zc)), s);
     else coarse_prolong_w32(m, h.cw, static_cast<float *>(const_cast<void *>(d.zc)), s);
 }
 

@@ -51,36 +51,31 @@ __global__ __launch_bounds__(256) void hat_kernel(int64_t E, int P, const double
     }
 }
 
-// One wavefront per element: s[c] = sum over the element's live nodes of
-// phi_c * f (f = the element's slice of a vector, scaled by w when given);
-// every lane ends with the eight totals (butterfly, fixed order).
-__device__ inline void wave_hat_sums(int P, const double *__restrict__ sqw, const double *__restrict__ f,
-                                     const uint8_t *__restrict__ mult, const double *__restrict__ inv,
-                                     double (&s)[8])
+// Totals of eight values over the wavefront.  Each of the first three steps
+// exchanges half of the values a lane still holds, so ten shuffles do the work
+// of the 48 of eight full butterflies, with the same pairs added at each
+// step (the same bits).  Returns the total of value lane >> 3.
+__device__ inline double wave_sum8(const double (&s)[8])
 {
-    const int P3 = P * P * P, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
+    double a[4], b[2];
+    const bool h5 = lane & 32, h4 = lane & 16, h3 = lane & 8;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) s[c] = 0.0;
-    for (int q = lane; q < P3; q += 64) {
-        double v = inv[q] > 0.0 ? f[q] : 0.0;
-        if (mult) v /= (double)mult[q];
-        double phi[8];
-        hat_weights(sqw, P, q, phi);
+    for (int q = 0; q < 4; ++q) a[q] = (h5 ? s[q + 4] : s[q]) + __shfl_xor(h5 ? s[q] : s[q + 4], 32, 64);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) s[c] += phi[c] * v;
-    }
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-        for (int off = 32; off > 0; off >>= 1) s[c] += __shfl_xor(s[c], off, 64);
+    for (int q = 0; q < 2; ++q) b[q] = (h4 ? a[q + 2] : a[q]) + __shfl_xor(h4 ? a[q] : a[q + 2], 16, 64);
+    double v = (h3 ? b[1] : b[0]) + __shfl_xor(h3 ? b[0] : b[1], 8, 64);
+    v += __shfl_xor(v, 4, 64);
+    v += __shfl_xor(v, 2, 64);
+    v += __shfl_xor(v, 1, 64);
+    return v;
 }
 
-__device__ inline double pick8(const double (&s)[8], int c)
+// 1/mult exactly: a node's copies are one or two along each axis, so its
+// multiplicity is a power of two and the reciprocal only sets an exponent
+__device__ inline double inv_mult_c(uint8_t m)
 {
-    double out = s[0];
-#pragma unroll
-    for (int q = 1; q < 8; ++q)
-        if (c == q) out = s[q];
-    return out;
+    return __longlong_as_double((long long)(1023 - __builtin_ctz(m)) << 52);
 }
 
 // E8[e][c'][c] = sum over element e's live nodes of phi_c' * w, w = A_e u_c
@@ -94,10 +89,16 @@ __global__ __launch_bounds__(256) void elem_coarse_kernel(int64_t E, int P, cons
     __syncthreads();
     const int P3 = P * P * P, lane = threadIdx.x & 63;
     for (int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); e < E; e += (int64_t)gridDim.x * 4) {
-        double s[8];
-        wave_hat_sums(P, sqw, w + e * P3, nullptr, inv + e * P3, s);
-        const double v = pick8(s, lane);
-        if (lane < 8) E8[e * 64 + lane * 8 + c] = v;
+        double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int q = lane; q < P3; q += 64) {
+            const double v = inv[e * P3 + q] > 0.0 ? w[e * P3 + q] : 0.0;
+            double phi[8];
+            hat_weights(sqw, P, q, phi);
+#pragma unroll
+            for (int h = 0; h < 8; ++h) s[h] += phi[h] * v;
+        }
+        const double v = wave_sum8(s);
+        if ((lane & 7) == 0) E8[e * 64 + lane + c] = v;
     }
 }
 
@@ -114,14 +115,6 @@ __device__ inline void hat_add(const double *__restrict__ sqw, int q, double v, 
     const double t00 = aj0 * ak0 * v, t10 = aj1 * ak0 * v, t01 = aj0 * ak1 * v, t11 = aj1 * ak1 * v;
     s[0] += ai0 * t00; s[1] += ai1 * t00; s[2] += ai0 * t10; s[3] += ai1 * t10;
     s[4] += ai0 * t01; s[5] += ai1 * t01; s[6] += ai0 * t11; s[7] += ai1 * t11;
-}
-
-// butterfly over the wavefront: every lane ends with the eight totals
-__device__ inline void wave_sum8(double (&s)[8])
-{
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-        for (int off = 32; off > 0; off >>= 1) s[c] += __shfl_xor(s[c], off, 64);
 }
 
 // partial8[e*8 + c] = sum over element e's live nodes of phi_c r / mult;
@@ -144,12 +137,11 @@ __global__ __launch_bounds__(256) void restrict_elem_kernel(int64_t E, const T *
 #pragma unroll
         for (int q = lane; q < P3; q += 64) {
             const T iv = ld_stream(inv + base + q);
-            const double v = iv > T(0) ? (double)ld_stream(r + base + q) / (double)mult[base + q] : 0.0;
+            const double v = iv > T(0) ? (double)ld_stream(r + base + q) * inv_mult_c(ld_stream(mult + base + q)) : 0.0;
             hat_add<N>(sqw, q, v, s);
         }
-        wave_sum8(s);
-        const double out = pick8(s, lane);
-        if (lane < 8) partial8[e * 8 + lane] = out;
+        const double out = wave_sum8(s);
+        if ((lane & 7) == 0) partial8[e * 8 + (lane >> 3)] = out;
     }
 }
 
@@ -192,7 +184,7 @@ __global__ __launch_bounds__(256) void update_restrict_kernel(int64_t E, const P
                 rv.x = rv.x - (float)alpha * wv.x;
                 rv.y = rv.y - (float)alpha * wv.y;
                 st_stream(rv, reinterpret_cast<float2 *>(r + base) + h);
-                const double ima = 1.0 / (double)(mm & 0xff), imb = 1.0 / (double)(mm >> 8);
+                const double ima = inv_mult_c((uint8_t)(mm & 0xff)), imb = inv_mult_c((uint8_t)(mm >> 8));
                 const double ra = (double)rv.x, rb = (double)rv.y;
                 rr += ra * ra * ima;
                 rr += rb * rb * imb;
@@ -210,16 +202,15 @@ __global__ __launch_bounds__(256) void update_restrict_kernel(int64_t E, const P
                 const T rv = ld_stream(r + o) - alpha * ld_stream(w + o);
                 st_stream(rv, r + o);
                 const T iv = ld_stream(inv + o);
-                const double im = 1.0 / (double)ld_stream(mult + o);
+                const double im = inv_mult_c(ld_stream(mult + o));
                 const double rd = (double)rv;
                 rr += rd * rd * im;
                 if (with_rz) rz += rd * (double)(iv * rv) * im;
                 hat_add<N>(sqw, q, iv > T(0) ? rd * im : 0.0, s);
             }
         }
-        wave_sum8(s);
-        const double out = pick8(s, lane);
-        if (lane < 8) partial8[e * 8 + lane] = out;
+        const double out = wave_sum8(s);
+        if ((lane & 7) == 0) partial8[e * 8 + (lane >> 3)] = out;
     }
     double v[2] = {rr, rz};
     block_reduce_store<2>(v, partial, 2);
@@ -288,27 +279,44 @@ __global__ __launch_bounds__(256) void cheb_kernel(int64_t nv, const int32_t *__
     }
 }
 
-// ADD: z += masked P z0; else z = masked P z0 (0 on masked nodes), rounded
-// to the precision of z
-template <bool ADD, typename TZ>
-__global__ __launch_bounds__(256) void prolong_kernel(int64_t E, int P, const int32_t *__restrict__ evert,
+// z = masked P z0, or with r z = inv r + masked P z0 (the whole
+// preconditioner with the Jacobi local part), rounded to the precision of z;
+// masked nodes (inv 0) get 0.  One lane per (i, j) column of an element, the
+// workgroup kPrElems elements: the eight corner values and the bilinear forms
+// of the column are taken once, a node costs two multiply-adds, and the pass
+// is bound by its 16 (24 with r) bytes per node.
+template <int N>
+constexpr int kPrElems = 256 / ((N + 1) * (N + 1)) > 0 ? 256 / ((N + 1) * (N + 1)) : 1;
+
+template <int N, bool JACOBI, typename TZ>
+__global__ __launch_bounds__(256) void prolong_kernel(int64_t E, const int32_t *__restrict__ evert,
                                                       const double *__restrict__ z0, const double *__restrict__ qw,
-                                                      const double *__restrict__ inv, TZ *__restrict__ z)
+                                                      const double *__restrict__ inv, const double *__restrict__ r,
+                                                      TZ *__restrict__ z)
 {
-    const int P3 = P * P * P;
-    const int64_t n = E * P3;
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x) {
-        if (!(inv[q] > 0.0)) {
-            if (!ADD) z[q] = TZ(0);
-            continue;
-        }
-        const int64_t e = q / P3;
-        double phi[8];
-        hat_weights(qw, P, (int)(q - e * P3), phi);
-        double s = 0.0;
+    constexpr int P = N + 1, P2 = P * P, P3 = P2 * P;
+    const int el = threadIdx.x / P2, ij = threadIdx.x - el * P2;
+    const int i = ij % P, j = ij / P;
+    const int64_t e = (int64_t)blockIdx.x * kPrElems<N> + el;
+    if (el >= kPrElems<N> || e >= E) return;
+    const int64_t o = e * P3 + ij;
+    double iv[P], rv[P];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) s += phi[c] * z0[evert[e * 8 + c]];
-        z[q] = ADD ? (TZ)(z[q] + s) : (TZ)s;
+    for (int k = 0; k < P; ++k) {
+        iv[k] = ld_stream(inv + o + k * P2);
+        if (JACOBI) rv[k] = ld_stream(r + o + k * P2);
+    }
+    double zc[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) zc[c] = z0[evert[e * 8 + c]];
+    const double ai0 = qw[i], ai1 = qw[P + i], aj0 = qw[j], aj1 = qw[P + j];
+    const double cs0 = aj0 * (ai0 * zc[0] + ai1 * zc[1]) + aj1 * (ai0 * zc[2] + ai1 * zc[3]);
+    const double cs1 = aj0 * (ai0 * zc[4] + ai1 * zc[5]) + aj1 * (ai0 * zc[6] + ai1 * zc[7]);
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        double v = iv[k] > 0.0 ? qw[k] * cs0 + qw[P + k] * cs1 : 0.0;
+        if (JACOBI) v += iv[k] * rv[k];
+        st_stream((TZ)v, z + o + k * P2);
     }
 }
 
@@ -632,31 +640,32 @@ int coarse_solve(sem_mesh *m, double *dot_pairs, const PcgState *st, hipStream_t
     return coarse_solve_w(m, coarse_work_own(m->coarse), dot_pairs, st, s);
 }
 
-void coarse_prolong_w(sem_mesh *m, const CoarseWork &W, double *z, bool add, hipStream_t s)
+template <bool JACOBI, typename TZ>
+static void prolong(sem_mesh *m, const double *z0, const double *r, TZ *z, hipStream_t s)
 {
     CoarseSpace *C = m->coarse;
-    const int64_t nL = m->h.nL;
-    if (add)
-        hipLaunchKernelGGL((prolong_kernel<true, double>), dim3(vec_blocks(nL)), dim3(256), 0, s, m->h.E, m->h.N + 1,
-                           C->evert, W.z0, C->qw, m->inv64, z);
-    else
-        hipLaunchKernelGGL((prolong_kernel<false, double>), dim3(vec_blocks(nL)), dim3(256), 0, s, m->h.E,
-                           m->h.N + 1, C->evert, W.z0, C->qw, m->inv64, z);
+    const int64_t E = m->h.E;
+#define SEM_PROLONG(n)                                                                                            \
+    hipLaunchKernelGGL((prolong_kernel<n, JACOBI, TZ>), dim3((unsigned)((E + kPrElems<n> - 1) / kPrElems<n>)),      \
+                       dim3(256), 0, s, E, C->evert, z0, C->qw, m->inv64, r, z)
+    SEM_COARSE_ORDER_SWITCH(m->h.N, SEM_PROLONG)
+#undef SEM_PROLONG
     SEM_HIP(hipGetLastError());
+}
+
+void coarse_prolong_w(sem_mesh *m, const CoarseWork &W, double *z, hipStream_t s)
+{
+    prolong<false, double>(m, W.z0, nullptr, z, s);
 }
 
 void coarse_prolong_w32(sem_mesh *m, const CoarseWork &W, float *z, hipStream_t s)
 {
-    CoarseSpace *C = m->coarse;
-    const int64_t nL = m->h.nL;
-    hipLaunchKernelGGL((prolong_kernel<false, float>), dim3(vec_blocks(nL)), dim3(256), 0, s, m->h.E, m->h.N + 1,
-                       C->evert, W.z0, C->qw, m->inv64, z);
-    SEM_HIP(hipGetLastError());
+    prolong<false, float>(m, W.z0, nullptr, z, s);
 }
 
-void coarse_prolong_add(sem_mesh *m, double *z, hipStream_t s)
+void coarse_jacobi_prolong(sem_mesh *m, const double *r, double *z, hipStream_t s)
 {
-    coarse_prolong_w(m, coarse_work_own(m->coarse), z, true, s);
+    prolong<true, double>(m, m->coarse->z0, r, z, s);
 }
 
 void launch_jacobi(int64_t n, const double *inv, const double *r, double *z, hipStream_t s)

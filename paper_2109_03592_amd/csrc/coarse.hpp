@@ -11,6 +11,17 @@
 
 namespace sem {
 
+// P z0 at one node: the trilinear combination of the element's corner values
+// (ev: its eight vertices, qw: the 1-D hat weights)
+__device__ inline double hat_value(const int32_t *__restrict__ ev, const double *__restrict__ z0,
+                                   const double *__restrict__ qw, int P, int i, int j, int k)
+{
+    double s = 0.0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) s += qw[(c & 1) * P + i] * qw[((c >> 1) & 1) * P + j] * qw[(c >> 2) * P + k] * z0[ev[c]];
+    return s;
+}
+
 constexpr int kMaxCoarseDotBlocks = 1024;  // partial pairs of the coarse dot, at most
 
 struct CoarseSpace {
@@ -50,8 +61,8 @@ CoarseWork coarse_work_own(const CoarseSpace *C);
 template <typename T>
 void coarse_restrict_w(sem_mesh *m, const CoarseWork &W, const T *r, const T *inv, hipStream_t s);
 int coarse_solve_w(sem_mesh *m, const CoarseWork &W, double *dot_pairs, const PcgState *st, hipStream_t s);
-// add: z += masked P z0; else z = masked P z0
-void coarse_prolong_w(sem_mesh *m, const CoarseWork &W, double *z, bool add, hipStream_t s);
+// z = masked P z0
+void coarse_prolong_w(sem_mesh *m, const CoarseWork &W, double *z, hipStream_t s);
 // z = masked P z0 rounded to FP32 (a mixed-precision batched slot's correction)
 void coarse_prolong_w32(sem_mesh *m, const CoarseWork &W, float *z, hipStream_t s);
 
@@ -73,8 +84,8 @@ void coarse_restrict(sem_mesh *m, const T *r, const T *inv, hipStream_t s);
 // given the (0, r0.z0) pairs there (returns their count, C->dot_blocks);
 // kernels skip when st->done.
 int coarse_solve(sem_mesh *m, double *dot_pairs, const PcgState *st, hipStream_t s);
-// z += masked P z0 (z0 from the last coarse_solve)
-void coarse_prolong_add(sem_mesh *m, double *z, hipStream_t s);
+// z = inv r + masked P z0 (z0 from the last coarse_solve)
+void coarse_jacobi_prolong(sem_mesh *m, const double *r, double *z, hipStream_t s);
 // z = inv r
 void launch_jacobi(int64_t n, const double *inv, const double *r, double *z, hipStream_t s);
 

@@ -29,8 +29,7 @@ struct SchwarzSpace {
     int64_t n_table = 0;       // distinct 1-D factors
     int dirichlet = 0;         // resolved Dirichlet face bits
     int32_t *tidx = nullptr;   // [E][3] table entry per direction
-    double *table = nullptr;   // [n_table][n*n + n]: S padded (zero rows/columns), then lam (1 beyond count)
-    int32_t *meta = nullptr;   // [n_table][2]: lo, count
+    double *table = nullptr;   // [n_table][2 n*n + n]: S by extended position (absent rows and modes 0), S^T, lam (1 for absent modes)
     double *zext = nullptr;    // [E][n^3] local solutions on the extended elements
     double *zs = nullptr;      // [nL] assembled Schwarz output
     std::vector<void *> allocations;
@@ -42,5 +41,10 @@ void schwarz_free(SchwarzSpace *S);
 // (0, <r, z>) partial pairs there (returns their count).  Kernels skip when
 // st->done.
 int schwarz_apply(sem_mesh *m, const double *r, double *z, double *pairs, const PcgState *st, hipStream_t s);
+// its two halves: the local solves of r on the extended elements (restrict_r:
+// also the mesh's coarse element sums of r), and their sum into z (add_coarse:
+// plus the prolonged coarse solution of the last coarse_solve)
+int schwarz_solves(sem_mesh *m, const double *r, double *pairs, bool restrict_r, const PcgState *st, hipStream_t s);
+void schwarz_assemble(sem_mesh *m, double *z, bool add_coarse, const PcgState *st, hipStream_t s);
 
 }  // namespace sem
