@@ -174,7 +174,9 @@ sem_status sem_get_operator_config(const sem_mesh *mesh, int *epw, int *grid);
  *     order 2..7 whatever the mesh size (for checking it; it is slower than
  *     the per-node kernel on small meshes and at low orders).
  * Both sum a node's copies in ascending local index, from 0, and set
- * Dirichlet nodes to 0 at every copy: results are bit-identical.  Changing
+ * Dirichlet nodes to 0 at every copy: results are bit-identical (and the
+ * resident CG of a small mesh, sem_pcg_solve, does the same by itself, with
+ * neither kernel).  Changing
  * the kind drops the captured CG iterations (re-captured on the next solve).
  * sem_get_gs_config returns the kind and whether the lattice kernel runs.
  * Errors: SEM_EINVAL (null mesh, unknown kind). */
@@ -340,6 +342,16 @@ void sem_solve_opts_default(sem_solve_opts *opts);
  * residual every poll_every iterations.  When the recursive residual meets
  * tol the true residual b - A x is recomputed; if it does not, CG restarts
  * from x (at most 3 times).
+ * On a small mesh (Jacobi, Poisson operator, no periodic axis of one element,
+ * orders 3..10, all elements fit on the device's compute units at once: up to
+ * about 10^6 points) the iterations run in one launch whose workgroups keep
+ * their elements on chip and exchange face values and partial sums; the copies
+ * of a node are summed as sem_gs sums them, poll_every and use_graph do not
+ * matter, and the dot products differ from the general iteration's (profile =
+ * 1) at rounding level.  It needs one more E-vector of device memory.  Solves
+ * of other threads that do not fit beside it wait for it.  If other work keeps
+ * its workgroups from running together for 20 ms, the general iteration takes
+ * over from the same state.
  * SEM_PREC_MIXED: defect correction -- r = b - A x in FP64, an FP32 PCG solves
  * A d = r/||r|| to inner_tol, x += ||r|| d in FP64, until the FP64 true
  * residual meets tol.  Needs SEM_WITH_FP32.

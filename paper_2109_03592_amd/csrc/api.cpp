@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -13,6 +14,7 @@
 #include "axgs_host.hpp"
 #include "coarse.hpp"
 #include "kernels.hpp"
+#include "resident.hpp"
 #include "schwarz.hpp"
 #include "sem_internal.hpp"
 
@@ -148,6 +150,7 @@ static void ensure_dtables(hipStream_t s)
     SEM_HIP(upload_dtables(d64.data(), d32.data(), s));
     SEM_HIP(upload_batch_dtables(d64.data(), d32.data(), s));
     SEM_HIP(upload_axgs_dtables(d64.data(), d32.data(), s));
+    SEM_HIP(upload_resident_dtables(d64.data(), d32.data(), s));
     SEM_HIP(hipStreamSynchronize(s));
     done[dev] = 1;
 }
@@ -699,6 +702,113 @@ static void pcg_start(sem_mesh *m, double stop2, int limit, hipStream_t s)
     SEM_HIP(hipMemsetAsync(Prec<T>::p(m), 0, sizeof(T) * nL, s));
 }
 
+// --- resident CG of a small mesh ---------------------------------------------
+// Compute units taken by resident runs in flight, per device: a run's
+// workgroups wait for each other, so all of them have to fit on the device
+// beside those of other threads' runs.  A run that does not fit waits for the
+// others (each holds its units for one launch, a few milliseconds), so what a
+// solve returns does not depend on what runs beside it.
+struct ResidentUnits {
+    std::mutex mu;
+    std::condition_variable cv;
+    std::vector<int> used;  // per device
+};
+static ResidentUnits &resident_units()
+{
+    static ResidentUnits u;
+    return u;
+}
+struct ResidentSeat {
+    int dev, n;
+    ResidentSeat(int device, int want, int cus) : dev(device), n(want)
+    {
+        ResidentUnits &u = resident_units();
+        std::unique_lock<std::mutex> lock(u.mu);
+        if ((int)u.used.size() <= dev) u.used.resize(dev + 1, 0);
+        u.cv.wait(lock, [&] { return u.used[dev] == 0 || u.used[dev] + n <= cus; });
+        u.used[dev] += n;
+    }
+    ~ResidentSeat()
+    {
+        ResidentUnits &u = resident_units();
+        {
+            std::lock_guard<std::mutex> lock(u.mu);
+            u.used[dev] -= n;
+        }
+        u.cv.notify_all();
+    }
+    ResidentSeat(const ResidentSeat &) = delete;
+    ResidentSeat &operator=(const ResidentSeat &) = delete;
+};
+
+// iterations of one launch, at most (a few milliseconds)
+constexpr int kResidentIters = 512;
+// longest wait of a resident run's workgroups for each other, in ticks of the
+// device's 100 MHz clock (20 ms)
+constexpr uint64_t kResidentWait = 2000000;
+
+// Whether the CG iteration of precision T takes the resident kernel on this
+// mesh: Jacobi on a lattice mesh of the Poisson operator that fits on the
+// chip.  There an iteration is bound by launches and latency.  Measured, us
+// per iteration in four launches and resident: 64 elements of order 7 32.5 and
+// 10.8, 1000 of them 43 and 15.8 (FP64), 1152 in FP32 38 and 14.2; with the
+// factors read every iteration 2028 elements of order 7 53 and 35 (FP64), 42
+// and 15.7 (FP32), 1210 of order 9 74 and 56, 55 and 18.  It won at every size
+// it takes; a mesh that does not fit is bound by memory more than by launches.
+template <typename T>
+static bool resident_for(const sem_mesh *m, ResidentShape &sh, int &cus)
+{
+    if (coarse_cg<T>(m) || schwarz_cg<T>(m) || m->helm || !m->gs_lattice_ok || (m->axgs && m->axgs->enabled) ||
+        m->h.nL >= INT32_MAX)
+        return false;
+    int lds = 0;
+    cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device) != hipSuccess ||
+        hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, m->device) != hipSuccess)
+        return false;
+    return resident_shape(m->h.N, m->h.E, sizeof(T), cus, (size_t)lds, sh);
+}
+
+// Up to k iterations resident on the chip; false when the workgroups did not
+// meet: nothing has changed then.  hs receives the state afterwards.
+template <typename T>
+static bool run_resident(sem_mesh *m, const ResidentShape &sh, int cus, int k, PcgState &hs, hipStream_t s)
+{
+    ResidentSeat seat(m->device, sh.nwg, cus);
+    if (!m->res_words) {
+        m->res_words = dalloc<uint64_t>(m, kResidentWords);
+        m->res_x = dalloc<double>(m, m->h.nL);
+        m->res_seq = 0;
+    }
+    if (m->res_seq == 0 || m->res_seq > UINT32_MAX - 2 * kResidentIters) {
+        SEM_HIP(hipMemsetAsync(m->res_words, 0, sizeof(uint64_t) * kResidentWords, s));
+        m->res_seq = 0;
+    }
+    ResidentParams<T> a{};
+    a.L = m->gsl;
+    a.E = m->h.E;
+    a.epw = sh.epw;
+    a.nwg = sh.nwg;
+    a.G = Prec<T>::G(m);
+    a.inv = Prec<T>::inv(m);
+    a.mult = m->mult;
+    a.r = Prec<T>::r(m);
+    a.p = Prec<T>::p(m);
+    a.x = Prec<T>::x(m);
+    a.w = Prec<T>::w(m);
+    a.xs = static_cast<T *>(m->res_x);
+    a.st = Prec<T>::st(m);
+    a.words = m->res_words;
+    a.seq = m->res_seq;
+    a.iters = std::min(k, kResidentIters);
+    a.wait_ticks = kResidentWait;
+    m->res_seq += (uint32_t)a.iters;
+    SEM_HIP(hipMemsetAsync(&a.st->pad, 0, sizeof(int), s));
+    SEM_HIP(launch_resident<T>(m->h.N, sh, a, s));
+    hs = read_state(a.st, s);
+    return hs.pad == 1;
+}
+
 // Plain CG loop on precision T from the current r (x, p set by the caller);
 // returns the final device state.
 template <typename T>
@@ -707,7 +817,11 @@ static PcgState cg_loop(sem_mesh *m, double stop2, int limit, int poll, bool gra
 {
     pcg_start<T>(m, stop2, limit, s);
     PcgState hs = read_state(Prec<T>::st(m), s);
+    ResidentShape sh;
+    int cus = 0;
+    bool resident = !prof && resident_for<T>(m, sh, cus);
     while (!hs.done) {
+        if (resident && (resident = run_resident<T>(m, sh, cus, kResidentIters, hs, s))) continue;
         run_iterations<T>(m, poll, graph, s, prof);
         hs = read_state(Prec<T>::st(m), s);
     }
@@ -735,7 +849,18 @@ static sem_status solve_fp64(sem_mesh *m, const double *b, double *x, const sem_
         int left = o.fixed_iters;
         Profiler prof;
         prof.m = m;
+        ResidentShape sh;
+        int cus = 0;
+        bool resident = !o.profile && resident_for<double>(m, sh, cus);
         while (left > 0) {
+            if (resident) {
+                PcgState hs;
+                resident = run_resident<double>(m, sh, cus, left, hs, s);
+                if (resident) {
+                    left -= std::min(left, kResidentIters);
+                    continue;
+                }
+            }
             const int k = std::min(left, poll);
             run_iterations<double>(m, k, o.use_graph != 0, s, o.profile ? &prof : nullptr);
             left -= k;

@@ -67,7 +67,7 @@ struct PcgState {
     int iters;         // iterations performed
     int done;          // 1 = converged, 2 = breakdown
     int limit;         // iteration limit
-    int pad;
+    int pad;           // verdict of a resident run (resident.hpp), else unused
 };
 
 // Device gather-scatter plan: CSR over global ids sorted in lattice order,
@@ -125,6 +125,11 @@ struct sem_mesh {
     // Krylov work space, allocated on the first solve
     double *x64 = nullptr, *r64 = nullptr, *p64 = nullptr, *w64 = nullptr;
     float *x32 = nullptr, *r32 = nullptr, *p32 = nullptr, *w32 = nullptr;
+    // resident CG of a small mesh (resident.hpp), allocated on the first solve
+    // that takes it: exchange words, x scratch, tags used so far
+    uint64_t *res_words = nullptr;
+    void *res_x = nullptr;
+    uint32_t res_seq = 0;
     double *partials = nullptr;   // reduction partials
     int64_t n_partials = 0;
     sem::PcgState *state = nullptr;  // [2]: FP64 solve, FP32 inner solve
