@@ -46,7 +46,7 @@ struct HostSlot {
     void *cbuf = nullptr;
     size_t cbuf_bytes = 0;
     CoarseWork cw{};
-    uint64_t serial = 0;     // unique per admission (keys the graphs that bake this slot's launches)
+    uint64_t serial = 0;     // unique per admission (the work tables follow it)
     std::chrono::steady_clock::time_point t0;
     double seconds = 0.0;
 };
@@ -58,19 +58,24 @@ struct Group {
     Item *ax_items = nullptr, *gs_items = nullptr, *vec_items = nullptr;
     int64_t *ax_first = nullptr, *ax_count = nullptr, *vec_first = nullptr, *vec_count = nullptr;
     double *ax_partial = nullptr, *vec_partial = nullptr;
+    Item *ce_items = nullptr, *cv_items = nullptr;
+    int64_t *cv_first = nullptr, *cv_count = nullptr;
+    double *cv_partial = nullptr;
     // capacities
-    int64_t cap_ax = 0, cap_gs = 0, cap_vec = 0;
+    int64_t cap_ax = 0, cap_gs = 0, cap_vec = 0, cap_ce = 0, cap_cv = 0;
     // host mirror
     std::vector<int32_t> h_slots;
     std::vector<Item> h_ax, h_gs, h_vec;
-    std::vector<int64_t> h_axf, h_axc, h_vf, h_vc;
+    std::vector<int64_t> h_axf, h_axc, h_vf, h_vc, h_cvf, h_cvc;
+    std::vector<Item> h_ce, h_cv;
+    std::vector<uint64_t> h_serial;  // admission of each slot in h_slots
+    int coarse_steps = 0;  // most Chebyshev steps of a slot with the coarse term (0: none has it)
     unsigned orders = 0;          // orders present in the tables
     int prec = 0;                 // precision of the operator launches (tile sizes follow it)
     hipGraphExec_t graph = nullptr;
     int graph_k = 0;
     unsigned graph_orders = 0;    // orders the cached graph launches
-    // the coarse-term launches the cached graph holds: (slot, its admission serial)
-    std::vector<std::pair<int, uint64_t>> graph_coarse;
+    int graph_steps = 0;          // coarse launches the cached graph holds
     GroupDev dev() const
     {
         GroupDev g;
@@ -85,6 +90,11 @@ struct Group {
         g.vec_count = vec_count;
         g.ax_partial = ax_partial;
         g.vec_partial = vec_partial;
+        g.ce_items = ce_items;
+        g.cv_items = cv_items;
+        g.cv_first = cv_first;
+        g.cv_count = cv_count;
+        g.cv_partial = cv_partial;
         return g;
     }
 };
@@ -98,6 +108,8 @@ struct sem_batch {
     std::vector<sem::HostSlot> slots;
     std::vector<sem::SlotDesc> h_desc;
     sem::SlotDesc *d_desc = nullptr;
+    std::vector<sem::CoarseDesc> h_cdesc;
+    sem::CoarseDesc *d_cdesc = nullptr;
     sem::PcgState *d_state = nullptr;   // 2 per slot
     double *d_scal = nullptr;           // 2 per slot
     sem::Group g64, g32, gres;          // CG64, CG32, residual
@@ -154,14 +166,16 @@ static void group_alloc(sem_batch *B, Group &g, int prec)
     g.ax_count = (int64_t *)balloc(B, sizeof(int64_t) * ms);
     g.vec_first = (int64_t *)balloc(B, sizeof(int64_t) * ms);
     g.vec_count = (int64_t *)balloc(B, sizeof(int64_t) * ms);
-    g.cap_ax = g.cap_gs = g.cap_vec = 0;
+    g.cv_first = (int64_t *)balloc(B, sizeof(int64_t) * ms);
+    g.cv_count = (int64_t *)balloc(B, sizeof(int64_t) * ms);
+    g.cap_ax = g.cap_gs = g.cap_vec = g.cap_ce = g.cap_cv = 0;
     SEM_HIP(hipMemset(g.counts, 0, sizeof(int64_t) * kCountSize));
 }
 
 // grow item tables (device addresses change: cached graphs are dropped; the
 // old buffers stay allocated until the batch is freed, since queued work may
 // still read them)
-static void group_reserve(sem_batch *B, Group &g, int64_t nax, int64_t ngs, int64_t nvec)
+static void group_reserve(sem_batch *B, Group &g, int64_t nax, int64_t ngs, int64_t nvec, int64_t nce, int64_t ncv)
 {
     bool grown = false;
     if (nax > g.cap_ax) {
@@ -184,6 +198,19 @@ static void group_reserve(sem_batch *B, Group &g, int64_t nax, int64_t ngs, int6
         g.cap_vec = c;
         grown = true;
     }
+    if (nce > g.cap_ce) {
+        const int64_t c = std::max<int64_t>({nce, 2 * g.cap_ce, 256});
+        g.ce_items = (Item *)balloc(B, sizeof(Item) * c);
+        g.cap_ce = c;
+        grown = true;
+    }
+    if (ncv > g.cap_cv) {
+        const int64_t c = std::max<int64_t>({ncv, 2 * g.cap_cv, 256});
+        g.cv_items = (Item *)balloc(B, sizeof(Item) * c);
+        g.cv_partial = (double *)balloc(B, sizeof(double) * c);
+        g.cap_cv = c;
+        grown = true;
+    }
     if (grown && g.graph) {
         hipGraphExecDestroy(g.graph);
         g.graph = nullptr;
@@ -194,6 +221,8 @@ static void group_reserve(sem_batch *B, Group &g, int64_t nax, int64_t ngs, int6
 static void group_build(sem_batch *B, Group &g, const std::vector<int> &ids, hipStream_t s)
 {
     g.h_slots.assign(ids.begin(), ids.end());
+    g.h_serial.clear();
+    for (int id : ids) g.h_serial.push_back(B->slots[id].serial);
     g.h_ax.clear();
     g.h_gs.clear();
     g.h_vec.clear();
@@ -228,8 +257,28 @@ static void group_build(sem_batch *B, Group &g, const std::vector<int> &ids, hip
         g.h_vc[id] = nv;
         for (int64_t t = 0; t < nv; ++t) g.h_vec.push_back(Item{id, (int32_t)t});
     }
+    // the coarse term: element and vertex items of every slot that takes it
+    g.h_ce.clear();
+    g.h_cv.clear();
+    g.h_cvf.assign(B->max_slots, 0);
+    g.h_cvc.assign(B->max_slots, 0);
+    g.coarse_steps = 0;
+    for (int id : ids) {
+        if (!B->h_desc[id].zc) continue;
+        const CoarseDesc &c = B->h_cdesc[id];
+        const int64_t ne = (c.E + kCoarseElems - 1) / kCoarseElems;
+        for (int64_t t = 0; t < ne; ++t) g.h_ce.push_back(Item{id, (int32_t)t});
+        const int64_t nv = (c.nvert + kCoarseRows - 1) / kCoarseRows;
+        g.h_cvf[id] = (int64_t)g.h_cv.size();
+        g.h_cvc[id] = nv;
+        for (int64_t t = 0; t < nv; ++t) g.h_cv.push_back(Item{id, (int32_t)t});
+        g.coarse_steps = std::max(g.coarse_steps, c.k);
+    }
     group_reserve(B, g, std::max<size_t>(g.h_ax.size(), 1), std::max<size_t>(g.h_gs.size(), 1),
-                  std::max<size_t>(g.h_vec.size(), 1));
+                  std::max<size_t>(g.h_vec.size(), 1), std::max<size_t>(g.h_ce.size(), 1),
+                  std::max<size_t>(g.h_cv.size(), 1));
+    counts[kCountCoarse] = (int64_t)g.h_ce.size();
+    counts[kCountCoarse + 1] = (int64_t)g.h_cv.size();
     counts[0] = (int64_t)ids.size();
     counts[1] = (int64_t)g.h_ax.size();
     counts[2] = (int64_t)g.h_gs.size();
@@ -243,6 +292,10 @@ static void group_build(sem_batch *B, Group &g, const std::vector<int> &ids, hip
     SEM_HIP(hipMemcpyAsync(g.ax_count, g.h_axc.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
     SEM_HIP(hipMemcpyAsync(g.vec_first, g.h_vf.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
     SEM_HIP(hipMemcpyAsync(g.vec_count, g.h_vc.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
+    SEM_HIP(hipMemcpyAsync(g.cv_first, g.h_cvf.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
+    SEM_HIP(hipMemcpyAsync(g.cv_count, g.h_cvc.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
+    if (!g.h_ce.empty()) SEM_HIP(hipMemcpyAsync(g.ce_items, g.h_ce.data(), sizeof(Item) * g.h_ce.size(), hipMemcpyHostToDevice, s));
+    if (!g.h_cv.empty()) SEM_HIP(hipMemcpyAsync(g.cv_items, g.h_cv.data(), sizeof(Item) * g.h_cv.size(), hipMemcpyHostToDevice, s));
     // host staging vectors must outlive the async copies
     SEM_HIP(hipStreamSynchronize(s));
 }
@@ -262,50 +315,25 @@ static void upload_desc(sem_batch *B, int id, hipStream_t s)
     SEM_HIP(hipMemcpyAsync(B->d_desc + id, &B->h_desc[id], sizeof(SlotDesc), hipMemcpyHostToDevice, s));
 }
 
-// The coarse term of one FP64 slot from its current r: restriction, the
-// Chebyshev coarse solve with r0.z0 reduced into crz, and zc = masked P z0.
-// Launched per slot (the coarse vectors are small); the kernels of a
-// converged slot skip or rewrite its own buffers only.
-// at_start: the CG start -- the kernels run whatever the slot's state says
-// (a mixed slot's FP32 state still holds the previous inner solve's flag).
-static void slot_coarse(sem_batch *B, int id, hipStream_t s, bool at_start = false)
+// the coarse term of the group's slots from their current r (nothing without
+// one); at_start: the CG start -- the kernels run whatever a slot's state says
+// (a mixed slot's FP32 state still holds the previous inner solve's flag)
+static void group_coarse(sem_batch *B, const Group &g, int prec, bool at_start, int steps, hipStream_t s)
 {
-    HostSlot &h = B->slots[id];
-    const SlotDesc &d = B->h_desc[id];
-    sem_mesh *m = h.mesh;
-    const int p = d.zc_prec;  // the precision of the slot's CG: FP64, or FP32 inner iterations
-    if (p == 0) coarse_restrict_w<double>(m, h.cw, static_cast<const double *>(d.r[0]), m->inv64, s);
-    else coarse_restrict_w<float>(m, h.cw, static_cast<const float *>(d.r[1]), m->inv32, s);
-    const int pairs = coarse_solve_w(m, h.cw, h.cw.dot, at_start ? nullptr : d.st + p, s);
-    SEM_HIP(launch_reduce_scalar(h.cw.dot, 2 * (int64_t)pairs, h.cw.rz, s));
-    if (p == 0) coarse_prolong_w(m, h.cw, static_cast<double *>(const_cast<void *>(d.zc)), s);
-    else coarse_prolong_w32(m, h.cw, static_cast<float *>(const_cast<void *>(d.zc)), s);
-}
-
-// the group's slots that take the coarse term in precision prec, with their
-// admission serials: a graph that baked a slot's coarse launches (its mesh's
-// coarse arrays, its work vectors) is replayed only for that same admission,
-// never for a later one that reuses the slot and its cached buffers
-static std::vector<std::pair<int, uint64_t>> coarse_slots(const sem_batch *B, const Group &g, int prec)
-{
-    std::vector<std::pair<int, uint64_t>> out;
-    for (int32_t id : g.h_slots)
-        if (B->h_desc[id].zc && B->h_desc[id].zc_prec == prec) out.emplace_back(id, B->slots[id].serial);
-    return out;
+    if (steps > 0) SEM_HIP(batch_coarse(prec, at_start, steps, B->d_desc, B->d_cdesc, g.dev(), launch_for(B, g), s));
 }
 
 // one CG iteration of every slot in g, precision prec
-static void enqueue_batch_iters(sem_batch *B, Group &g, int prec, int k, unsigned orders, hipStream_t s)
+static void enqueue_batch_iters(sem_batch *B, Group &g, int prec, int k, unsigned orders, int steps, hipStream_t s)
 {
     const GroupDev gd = g.dev();
     const BatchLaunch L = launch_for(B, orders, g.prec);
-    const auto cs = coarse_slots(B, g, prec);
     for (int it = 0; it < k; ++it) {
         SEM_HIP(batch_ax(prec, 2, B->d_desc, gd, L, s));
         SEM_HIP(batch_gs(prec, 1, B->d_desc, gd, L, s));
         SEM_HIP(batch_reduce_sigma(prec, B->d_desc, gd, L, s));
         SEM_HIP(batch_update(prec, B->d_desc, gd, L, s));
-        for (const auto &c : cs) slot_coarse(B, c.first, s);
+        group_coarse(B, g, prec, false, steps, s);
         SEM_HIP(batch_reduce_rho(prec, B->d_desc, gd, L, s));
     }
 }
@@ -314,14 +342,15 @@ static void run_batch_iters(sem_batch *B, Group &g, int prec, int k, bool use_gr
 {
     if (g.h_slots.empty()) return;
     if (!use_graph) {
-        enqueue_batch_iters(B, g, prec, k, g.orders, s);
+        enqueue_batch_iters(B, g, prec, k, g.orders, g.coarse_steps, s);
         return;
     }
-    // a cached graph serves any membership whose orders it launches (an
-    // order without items exits at once) and whose coarse-term slots it holds
-    const auto cs = coarse_slots(B, g, prec);
-    if (!g.graph || g.graph_k != k || (g.orders & ~g.graph_orders) != 0 || cs != g.graph_coarse) {
+    // a cached graph serves any membership whose orders and coarse phases it
+    // launches (an order or a phase without items exits at once)
+    if (!g.graph || g.graph_k != k || (g.orders & ~g.graph_orders) != 0 ||
+        g.coarse_steps > g.graph_steps) {
         const unsigned orders = g.orders | (g.graph ? g.graph_orders : 0u);
+        const int steps = std::max(g.coarse_steps, g.graph ? g.graph_steps : 0);
         if (g.graph) {
             SEM_HIP(hipGraphExecDestroy(g.graph));
             g.graph = nullptr;
@@ -330,7 +359,7 @@ static void run_batch_iters(sem_batch *B, Group &g, int prec, int k, bool use_gr
         hipGraph_t gr = nullptr;
         SEM_HIP(hipStreamBeginCapture(B->capture, hipStreamCaptureModeThreadLocal));
         try {
-            enqueue_batch_iters(B, g, prec, k, orders, B->capture);
+            enqueue_batch_iters(B, g, prec, k, orders, steps, B->capture);
         } catch (...) {
             hipStreamEndCapture(B->capture, &gr);
             if (gr) hipGraphDestroy(gr);
@@ -344,7 +373,7 @@ static void run_batch_iters(sem_batch *B, Group &g, int prec, int k, bool use_gr
         g.graph = ex;
         g.graph_k = k;
         g.graph_orders = orders;
-        g.graph_coarse = cs;
+        g.graph_steps = steps;
     }
     SEM_HIP(hipGraphLaunch(g.graph, s));
 }
@@ -371,7 +400,7 @@ static void start_cg(sem_batch *B, const std::vector<int> &ids, int prec, hipStr
     Group &g = B->gres;
     group_build(B, g, ids, s);
     // the coarse term of the start residual; its r0.z0 joins rho
-    for (const auto &c : coarse_slots(B, g, prec)) slot_coarse(B, c.first, s, true);
+    group_coarse(B, g, prec, true, g.coarse_steps, s);
     SEM_HIP(batch_cg_init(prec, B->d_desc, g.dev(), launch_for(B, g), s));
 }
 
@@ -483,7 +512,7 @@ static void step_batch(sem_batch *B, int k, bool use_graph, hipStream_t s)
         group_build(B, g, to32, s);
         SEM_HIP(batch_to_fp32(B->d_desc, g.dev(), launch_for(B, g), s));
         // the coarse term of the FP32 start residual; its r0.z0 joins rho
-        for (const auto &c : coarse_slots(B, g, 1)) slot_coarse(B, c.first, s, true);
+        group_coarse(B, g, 1, true, g.coarse_steps, s);
         SEM_HIP(batch_cg_init(1, B->d_desc, g.dev(), launch_for(B, g), s));
     }
     // 3. CG iterations
@@ -492,8 +521,16 @@ static void step_batch(sem_batch *B, int k, bool use_graph, hipStream_t s)
         if (B->slots[id].phase == PH_CG64) cg64.push_back(id);
         if (B->slots[id].phase == PH_CG32) cg32.push_back(id);
     }
-    if (cg64 != B->g64.h_slots) group_build(B, B->g64, cg64, s);
-    if (cg32 != B->g32.h_slots) group_build(B, B->g32, cg32, s);
+    // the tables follow the slots and their admissions (a slot retired after a
+    // breakdown and admitted again is another solve under the same number)
+    auto stale = [&](const Group &g, const std::vector<int> &ids) {
+        if (ids != g.h_slots) return true;
+        for (size_t q = 0; q < ids.size(); ++q)
+            if (B->slots[ids[q]].serial != g.h_serial[q]) return true;
+        return false;
+    };
+    if (stale(B->g64, cg64)) group_build(B, B->g64, cg64, s);
+    if (stale(B->g32, cg32)) group_build(B, B->g32, cg32, s);
     if (!cg64.empty()) run_batch_iters(B, B->g64, 0, k, use_graph, s);
     if (!cg32.empty()) run_batch_iters(B, B->g32, 1, k, use_graph, s);
     if (cg64.empty() && cg32.empty()) return;
@@ -689,8 +726,34 @@ static int admit_slot(sem_batch *B, sem_mesh *m, const double *b, double *x, con
     d.st = B->d_state + 2 * id;
     d.scal = B->d_scal + 2 * id;
     d.zc = coarse ? cbuf : nullptr;
-    d.crz = coarse ? h.cw.rz : nullptr;
     d.zc_prec = zc_prec;
+    if (coarse) {
+        const CoarseSpace *C = m->coarse;
+        CoarseDesc &c = B->h_cdesc[id];
+        c = CoarseDesc();
+        c.N = hm.N;
+        c.k = C->k;
+        c.E = hm.E;
+        c.nvert = C->nvert;
+        c.inv_theta = C->inv_theta;
+        c.evert = C->evert;
+        c.v_off = C->v_off;
+        c.v_idx = C->v_idx;
+        c.a_off = C->a_off;
+        c.a_col = C->a_col;
+        c.a_val = C->a_val;
+        c.d0inv = C->d0inv;
+        c.qw = C->qw;
+        c.coef = C->coef;
+        c.inv64 = m->inv64;
+        c.partial8 = h.cw.partial8;
+        c.r0 = h.cw.r0;
+        c.z0 = h.cw.z0;
+        c.res = h.cw.res;
+        c.d[0] = h.cw.d;
+        c.d[1] = h.cw.tmp;
+        SEM_HIP(hipMemcpyAsync(B->d_cdesc + id, &c, sizeof(CoarseDesc), hipMemcpyHostToDevice, s));
+    }
     SEM_HIP(hipMemsetAsync(d.st, 0, 2 * sizeof(PcgState), s));
     // mixed slots start with a residual of the caller's x: zero it unless it
     // is the initial guess (FP64 slots without a guess zero it themselves)
@@ -738,7 +801,9 @@ sem_status sem_batch_create(int max_slots, size_t device_budget, void *stream, s
             SEM_HIP(hipGetDevice(&B->device));
             B->slots.assign(max_slots, HostSlot());
             B->h_desc.assign(max_slots, SlotDesc());
+            B->h_cdesc.assign(max_slots, CoarseDesc());
             B->d_desc = (SlotDesc *)balloc(B, sizeof(SlotDesc) * max_slots);
+            B->d_cdesc = (CoarseDesc *)balloc(B, sizeof(CoarseDesc) * max_slots);
             B->d_state = (PcgState *)balloc(B, sizeof(PcgState) * 2 * max_slots);
             B->d_scal = (double *)balloc(B, sizeof(double) * 2 * max_slots);
             SEM_HIP(hipMemsetAsync(B->d_state, 0, sizeof(PcgState) * 2 * max_slots, s));

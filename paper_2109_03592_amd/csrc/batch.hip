@@ -345,6 +345,17 @@ __device__ inline void slot_sum(const double *__restrict__ part, int64_t first, 
     for (int q = 0; q < NV; ++q) out[q] = red[q][0];
 }
 
+// <r, P z0> = r0.z0 of a slot with the coarse term (else 0): the sum of its
+// vertex items' partials
+__device__ inline double slot_coarse_dot(const SlotDesc &sd, const GroupDev &g, int sl, int prec)
+{
+    if (!sd.zc || sd.zc_prec != prec) return 0.0;  // uniform over the workgroup
+    double s[1];
+    __syncthreads();
+    slot_sum<1>(g.cv_partial, g.cv_first[sl], g.cv_count[sl], s);
+    return s[0];
+}
+
 __device__ inline int group_slot(const GroupDev &g)
 {
     const int64_t ns = g.counts[0];
@@ -375,7 +386,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_reduce_rho_kernel(SlotDesc 
     if (st->done) return;
     double s[2];
     slot_sum<2>(g.vec_partial, g.vec_first[sl], g.vec_count[sl], s);
-    if (slots[sl].crz && slots[sl].zc_prec == prec) s[1] += *slots[sl].crz;  // <r, P z0> = r0.z0
+    s[1] += slot_coarse_dot(slots[sl], g, sl, prec);
     if (threadIdx.x == 0) {
         st->iters += 1;
         st->rr = s[0];
@@ -396,7 +407,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_reduce_init_kernel(SlotDesc
     PcgState *st = sd.st + prec;
     double s[2];
     slot_sum<2>(g.vec_partial, g.vec_first[sl], g.vec_count[sl], s);
-    if (sd.crz && sd.zc_prec == prec) s[1] += *sd.crz;
+    s[1] += slot_coarse_dot(sd, g, sl, prec);
     if (threadIdx.x == 0) {
         st->rr = s[0];
         st->rho = s[1];

@@ -20,6 +20,11 @@ namespace sem {
 constexpr int kBatchBlock = 256;       // threads per workgroup of every batched kernel
 constexpr int kGsChunk = 256;          // gather-scatter ids per item
 constexpr int kVecChunk = 256 * 8;     // vector points per item
+// coarse items: elements of the restriction and prolongation (one per
+// wavefront; 16 of them in turn took 32 us where four at once take 8) and
+// vertices, eight lanes each
+constexpr int kCoarseElems = 4;
+constexpr int kCoarseRows = 32;
 
 struct Item {
     int32_t slot;
@@ -49,18 +54,31 @@ struct SlotDesc {
     // coarse term of Eq. 6 (a mesh with a coarse space; else null): zc =
     // masked P z0 of the current r, in the precision zc_prec of the slot's CG
     // (0 FP64, 1 FP32 for a mixed slot's inner iterations), added in the
-    // operator's p update; crz = r0.z0, added to <r, z> after the slot's partials
+    // operator's p update; r0.z0, the sum of the slot's cv partials, joins <r, z>
     const void *zc;
-    const double *crz;
     int zc_prec;
     int pad3;
+};
+
+// The coarse term of one slot (csrc/coarse.hpp), for the batched coarse
+// kernels: its mesh's coarse space and its own work vectors.
+struct CoarseDesc {
+    int N, k;             // order, Chebyshev steps
+    int64_t E, nvert;
+    double inv_theta;
+    const int32_t *evert, *v_off, *v_idx, *a_off, *a_col;
+    const double *a_val, *d0inv, *qw, *coef;  // coef: [k] c1, [k] c2
+    const double *inv64;
+    double *partial8, *r0, *z0, *res, *d[2];
 };
 
 // counts[] of a group: [0] n_slots, [1] ax items, [2] gs items, [3] vec
 // items, then per order N the operator items' [first, count] at
 // kCountAxRange + 2N (operator items are sorted by order, then slot)
 constexpr int kCountAxRange = 4;
-constexpr int kCountSize = kCountAxRange + 2 * (SEM_MAX_ORDER + 1);
+// coarse slots' element items, vertex items
+constexpr int kCountCoarse = kCountAxRange + 2 * (SEM_MAX_ORDER + 1);
+constexpr int kCountSize = kCountCoarse + 2;
 
 // Device view of one group (all arrays sized for the batch capacity).
 struct GroupDev {
@@ -73,6 +91,9 @@ struct GroupDev {
     const int64_t *vec_count;
     double *ax_partial;       // per ax item
     double *vec_partial;      // 2 per vec item
+    const Item *ce_items, *cv_items;  // coarse: element chunks, vertex chunks
+    const int64_t *cv_first, *cv_count;
+    double *cv_partial;       // per cv item: its share of r0.z0
 };
 
 struct BatchLaunch {
@@ -102,6 +123,12 @@ hipError_t batch_to_fp32(const SlotDesc *slots, const GroupDev &g, const BatchLa
 hipError_t batch_finish(int prec, const SlotDesc *slots, const GroupDev &g, const BatchLaunch &L, hipStream_t s);
 // mixed: x64 += sqrt(scal[1]) x32
 hipError_t batch_axpy(const SlotDesc *slots, const GroupDev &g, const BatchLaunch &L, hipStream_t s);
+// The coarse term of every slot of the group that has one, from its current
+// r in precision prec: element sums, vertex sums, Chebyshev steps (r0.z0 in
+// the cv partials) and zc = masked P z0.  steps: the largest step count among
+// the slots.  at_start: whatever the slots' states say.
+hipError_t batch_coarse(int prec, bool at_start, int steps, const SlotDesc *slots, const CoarseDesc *cdesc,
+                        const GroupDev &g, const BatchLaunch &L, hipStream_t s);
 // orders the batched operator is built for
 bool batch_order_supported(int N);
 

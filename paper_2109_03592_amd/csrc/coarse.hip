@@ -20,6 +20,7 @@
 #include <utility>
 #include <vector>
 
+#include "batch.hpp"
 #include "coarse.hpp"
 #include "kernels.hpp"
 #include "operator.hpp"
@@ -117,8 +118,26 @@ __device__ inline void hat_add(const double *__restrict__ sqw, int q, double v, 
     s[4] += ai0 * t01; s[5] += ai1 * t01; s[6] += ai0 * t11; s[7] += ai1 * t11;
 }
 
-// partial8[e*8 + c] = sum over element e's live nodes of phi_c r / mult;
-// one wavefront per element
+// partial8[e*8 + c] = sum over element e's live nodes of phi_c r / mult, by
+// one wavefront (sqw: the hat weights in LDS)
+template <typename T, int N>
+__device__ inline void restrict_element(int64_t e, const T *__restrict__ r, const uint8_t *__restrict__ mult,
+                                        const T *__restrict__ inv, const double *sqw, double *__restrict__ partial8)
+{
+    constexpr int P = N + 1, P3 = P * P * P;
+    const int lane = threadIdx.x & 63;
+    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    const int64_t base = e * P3;
+#pragma unroll
+    for (int q = lane; q < P3; q += 64) {
+        const T iv = ld_stream(inv + base + q);
+        const double v = iv > T(0) ? (double)ld_stream(r + base + q) * inv_mult_c(ld_stream(mult + base + q)) : 0.0;
+        hat_add<N>(sqw, q, v, s);
+    }
+    const double out = wave_sum8(s);
+    if ((lane & 7) == 0) partial8[e * 8 + (lane >> 3)] = out;
+}
+
 template <typename T, int N>
 __global__ __launch_bounds__(256) void restrict_elem_kernel(int64_t E, const T *__restrict__ r,
                                                             const uint8_t *__restrict__ mult,
@@ -126,23 +145,12 @@ __global__ __launch_bounds__(256) void restrict_elem_kernel(int64_t E, const T *
                                                             const double *__restrict__ qw,
                                                             double *__restrict__ partial8)
 {
-    constexpr int P = N + 1, P3 = P * P * P;
+    constexpr int P = N + 1;
     __shared__ double sqw[2 * P];
     if (threadIdx.x < 2 * P) sqw[threadIdx.x] = qw[threadIdx.x];
     __syncthreads();
-    const int lane = threadIdx.x & 63;
-    for (int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); e < E; e += (int64_t)gridDim.x * 4) {
-        double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        const int64_t base = e * P3;
-#pragma unroll
-        for (int q = lane; q < P3; q += 64) {
-            const T iv = ld_stream(inv + base + q);
-            const double v = iv > T(0) ? (double)ld_stream(r + base + q) * inv_mult_c(ld_stream(mult + base + q)) : 0.0;
-            hat_add<N>(sqw, q, v, s);
-        }
-        const double out = wave_sum8(s);
-        if ((lane & 7) == 0) partial8[e * 8 + (lane >> 3)] = out;
-    }
+    for (int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); e < E; e += (int64_t)gridDim.x * 4)
+        restrict_element<T, N>(e, r, mult, inv, sqw, partial8);
 }
 
 // CG update with the coarse restriction fused in: r -= alpha w, the partial
@@ -289,16 +297,13 @@ template <int N>
 constexpr int kPrElems = 256 / ((N + 1) * (N + 1)) > 0 ? 256 / ((N + 1) * (N + 1)) : 1;
 
 template <int N, bool JACOBI, typename TZ>
-__global__ __launch_bounds__(256) void prolong_kernel(int64_t E, const int32_t *__restrict__ evert,
-                                                      const double *__restrict__ z0, const double *__restrict__ qw,
-                                                      const double *__restrict__ inv, const double *__restrict__ r,
-                                                      TZ *__restrict__ z)
+__device__ inline void prolong_column(int64_t e, int ij, const int32_t *__restrict__ evert,
+                                      const double *__restrict__ z0, const double *__restrict__ qw,
+                                      const double *__restrict__ inv, const double *__restrict__ r,
+                                      TZ *__restrict__ z)
 {
     constexpr int P = N + 1, P2 = P * P, P3 = P2 * P;
-    const int el = threadIdx.x / P2, ij = threadIdx.x - el * P2;
     const int i = ij % P, j = ij / P;
-    const int64_t e = (int64_t)blockIdx.x * kPrElems<N> + el;
-    if (el >= kPrElems<N> || e >= E) return;
     const int64_t o = e * P3 + ij;
     double iv[P], rv[P];
 #pragma unroll
@@ -318,6 +323,20 @@ __global__ __launch_bounds__(256) void prolong_kernel(int64_t E, const int32_t *
         if (JACOBI) v += iv[k] * rv[k];
         st_stream((TZ)v, z + o + k * P2);
     }
+}
+
+// z = inv r + masked P z0
+template <int N>
+__global__ __launch_bounds__(256) void prolong_kernel(int64_t E, const int32_t *__restrict__ evert,
+                                                      const double *__restrict__ z0, const double *__restrict__ qw,
+                                                      const double *__restrict__ inv, const double *__restrict__ r,
+                                                      double *__restrict__ z)
+{
+    constexpr int P2 = (N + 1) * (N + 1);
+    const int el = threadIdx.x / P2, ij = threadIdx.x - el * P2;
+    const int64_t e = (int64_t)blockIdx.x * kPrElems<N> + el;
+    if (el >= kPrElems<N> || e >= E) return;
+    prolong_column<N, true, double>(e, ij, evert, z0, qw, inv, r, z);
 }
 
 __global__ void jacobi_kernel(int64_t n, const double *__restrict__ inv, const double *__restrict__ r,
@@ -500,6 +519,10 @@ CoarseSpace *coarse_build(sem_mesh *m, int k, double frac, hipStream_t s)
             C->c2[j] = 2.0 * rho_new / delta;
             rho = rho_new;
         }
+        std::vector<double> coef(C->c1);
+        coef.insert(coef.end(), C->c2.begin(), C->c2.end());
+        C->coef = cmalloc<double>(C, coef.size());
+        SEM_HIP(hipMemcpyAsync(C->coef, coef.data(), sizeof(double) * coef.size(), hipMemcpyHostToDevice, s));
         C->r0 = cmalloc<double>(C, C->nvert);
         C->z0 = cmalloc<double>(C, C->nvert);
         C->res = cmalloc<double>(C, C->nvert);
@@ -552,7 +575,7 @@ static int64_t round32(int64_t n) { return (n + 31) / 32 * 32; }
 
 int64_t coarse_work_doubles(const CoarseSpace *C, int64_t E)
 {
-    return round32(E * 8) + 5 * round32(C->nvert) + round32(2 * (int64_t)C->dot_blocks) + 32;
+    return round32(E * 8) + 5 * round32(C->nvert);
 }
 
 CoarseWork coarse_work_carve(const CoarseSpace *C, int64_t E, double *base)
@@ -570,64 +593,40 @@ CoarseWork coarse_work_carve(const CoarseSpace *C, int64_t E, double *base)
     W.res = take(C->nvert);
     W.d = take(C->nvert);
     W.tmp = take(C->nvert);
-    W.dot = take(2 * (int64_t)C->dot_blocks);
-    W.rz = take(1);
-    return W;
-}
-
-CoarseWork coarse_work_own(const CoarseSpace *C)
-{
-    CoarseWork W;
-    W.partial8 = C->partial8;
-    W.r0 = C->r0;
-    W.z0 = C->z0;
-    W.res = C->res;
-    W.d = C->d;
-    W.tmp = C->tmp;
-    W.dot = nullptr;
-    W.rz = nullptr;
     return W;
 }
 
 template <typename T>
-void coarse_restrict_w(sem_mesh *m, const CoarseWork &W, const T *r, const T *inv, hipStream_t s)
+void coarse_restrict(sem_mesh *m, const T *r, const T *inv, hipStream_t s)
 {
     CoarseSpace *C = m->coarse;
     const int64_t E = m->h.E;
 #define SEM_RES(n)                                                                                                  \
     hipLaunchKernelGGL((restrict_elem_kernel<T, n>), dim3(elem_blocks(E)), dim3(256), 0, s, E, r, m->mult, inv, \
-                       C->qw, W.partial8)
+                       C->qw, C->partial8)
     SEM_COARSE_ORDER_SWITCH(m->h.N, SEM_RES)
 #undef SEM_RES
     SEM_HIP(hipGetLastError());
 }
-template void coarse_restrict_w<double>(sem_mesh *, const CoarseWork &, const double *, const double *, hipStream_t);
-template void coarse_restrict_w<float>(sem_mesh *, const CoarseWork &, const float *, const float *, hipStream_t);
-
-template <typename T>
-void coarse_restrict(sem_mesh *m, const T *r, const T *inv, hipStream_t s)
-{
-    coarse_restrict_w<T>(m, coarse_work_own(m->coarse), r, inv, s);
-}
 template void coarse_restrict<double>(sem_mesh *, const double *, const double *, hipStream_t);
 template void coarse_restrict<float>(sem_mesh *, const float *, const float *, hipStream_t);
 
-int coarse_solve_w(sem_mesh *m, const CoarseWork &W, double *dot_pairs, const PcgState *st, hipStream_t s)
+int coarse_solve(sem_mesh *m, double *dot_pairs, const PcgState *st, hipStream_t s)
 {
     CoarseSpace *C = m->coarse;
     const int64_t nv = C->nvert;
     hipLaunchKernelGGL(restrict_vert_kernel, dim3(cgrid(nv, 4096)), dim3(256), 0, s, nv, C->v_off, C->v_idx,
-                       W.partial8, C->d0inv, C->inv_theta, W.r0, W.z0, W.res, W.d, st);
+                       C->partial8, C->d0inv, C->inv_theta, C->r0, C->z0, C->res, C->d, st);
     SEM_HIP(hipGetLastError());
-    double *din = W.d, *dout = W.tmp;
+    double *din = C->d, *dout = C->tmp;
     for (int j = 0; j < C->k; ++j) {
         if (j + 1 < C->k) {
             hipLaunchKernelGGL(cheb_kernel<false>, dim3(C->dot_blocks), dim3(256), 0, s, nv, C->a_off, C->a_col,
-                               C->a_val, C->c1[j], C->c2[j], C->d0inv, din, dout, W.z0, W.res, W.r0, nullptr, st);
+                               C->a_val, C->c1[j], C->c2[j], C->d0inv, din, dout, C->z0, C->res, C->r0, nullptr, st);
             std::swap(din, dout);
         } else {
             hipLaunchKernelGGL(cheb_kernel<true>, dim3(C->dot_blocks), dim3(256), 0, s, nv, C->a_off, C->a_col,
-                               C->a_val, C->c1[j], C->c2[j], C->d0inv, din, dout, W.z0, W.res, W.r0, dot_pairs,
+                               C->a_val, C->c1[j], C->c2[j], C->d0inv, din, dout, C->z0, C->res, C->r0, dot_pairs,
                                st);
         }
     }
@@ -635,37 +634,178 @@ int coarse_solve_w(sem_mesh *m, const CoarseWork &W, double *dot_pairs, const Pc
     return C->dot_blocks;
 }
 
-int coarse_solve(sem_mesh *m, double *dot_pairs, const PcgState *st, hipStream_t s)
-{
-    return coarse_solve_w(m, coarse_work_own(m->coarse), dot_pairs, st, s);
-}
-
-template <bool JACOBI, typename TZ>
-static void prolong(sem_mesh *m, const double *z0, const double *r, TZ *z, hipStream_t s)
+void coarse_jacobi_prolong(sem_mesh *m, const double *r, double *z, hipStream_t s)
 {
     CoarseSpace *C = m->coarse;
     const int64_t E = m->h.E;
-#define SEM_PROLONG(n)                                                                                            \
-    hipLaunchKernelGGL((prolong_kernel<n, JACOBI, TZ>), dim3((unsigned)((E + kPrElems<n> - 1) / kPrElems<n>)),      \
-                       dim3(256), 0, s, E, C->evert, z0, C->qw, m->inv64, r, z)
+#define SEM_PROLONG(n)                                                                                     \
+    hipLaunchKernelGGL(prolong_kernel<n>, dim3((unsigned)((E + kPrElems<n> - 1) / kPrElems<n>)), dim3(256), 0, s, E, \
+                       C->evert, C->z0, C->qw, m->inv64, r, z)
     SEM_COARSE_ORDER_SWITCH(m->h.N, SEM_PROLONG)
 #undef SEM_PROLONG
     SEM_HIP(hipGetLastError());
 }
 
-void coarse_prolong_w(sem_mesh *m, const CoarseWork &W, double *z, hipStream_t s)
+// ---------------------------------------------------------------------------
+// The coarse term of a batch's slots.  Each phase is one launch over the work
+// items of all slots that take part, whatever their orders and sizes (slot by
+// slot, the eight small launches of a slot took about 80 us an iteration).
+
+#define SEM_BATCH_COARSE_ORDERS(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10)
+
+template <typename T>
+__device__ inline bool coarse_skips(const SlotDesc &sd, int at_start)
 {
-    prolong<false, double>(m, W.z0, nullptr, z, s);
+    return !at_start && sd.st[sizeof(T) == 8 ? 0 : 1].done;
 }
 
-void coarse_prolong_w32(sem_mesh *m, const CoarseWork &W, float *z, hipStream_t s)
+// element sums of the items' elements, one wavefront per element
+template <typename T>
+__global__ __launch_bounds__(256) void batch_restrict_kernel(const SlotDesc *__restrict__ slots,
+                                                             const CoarseDesc *__restrict__ cd, GroupDev g,
+                                                             int at_start)
 {
-    prolong<false, float>(m, W.z0, nullptr, z, s);
+    constexpr int prec = sizeof(T) == 8 ? 0 : 1;
+    __shared__ double sqw[2 * (SEM_MAX_ORDER + 1)];
+    const int64_t n = g.counts[kCountCoarse];
+    for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
+        const Item item = g.ce_items[it];
+        const SlotDesc &sd = slots[item.slot];
+        const CoarseDesc &C = cd[item.slot];
+        if (coarse_skips<T>(sd, at_start)) continue;  // uniform over the workgroup
+        __syncthreads();
+        if ((int)threadIdx.x < 2 * (C.N + 1)) sqw[threadIdx.x] = C.qw[threadIdx.x];
+        __syncthreads();
+        const T *r = static_cast<const T *>(sd.r[prec]), *inv = static_cast<const T *>(sd.inv[prec]);
+        const int64_t e0 = (int64_t)item.local * kCoarseElems;
+        const int64_t e1 = e0 + kCoarseElems < C.E ? e0 + kCoarseElems : C.E;
+        for (int64_t e = e0 + (threadIdx.x >> 6); e < e1; e += 4) {
+            switch (C.N) {
+#define SEM_BRC(nn) \
+            case nn: restrict_element<T, nn>(e, r, sd.mult, inv, sqw, C.partial8); break;
+                SEM_BATCH_COARSE_ORDERS(SEM_BRC)
+#undef SEM_BRC
+            }
+        }
+    }
 }
 
-void coarse_jacobi_prolong(sem_mesh *m, const double *r, double *z, hipStream_t s)
+// zc = masked P z0 on the items' elements
+template <typename T>
+__global__ __launch_bounds__(256) void batch_prolong_kernel(const SlotDesc *__restrict__ slots,
+                                                            const CoarseDesc *__restrict__ cd, GroupDev g,
+                                                            int at_start)
 {
-    prolong<true, double>(m, m->coarse->z0, r, z, s);
+    const int64_t n = g.counts[kCountCoarse];
+    for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
+        const Item item = g.ce_items[it];
+        const SlotDesc &sd = slots[item.slot];
+        const CoarseDesc &C = cd[item.slot];
+        if (coarse_skips<T>(sd, at_start)) continue;
+        T *zc = static_cast<T *>(const_cast<void *>(sd.zc));
+        const int P2 = (C.N + 1) * (C.N + 1);
+        const int64_t e0 = (int64_t)item.local * kCoarseElems;
+        const int64_t ne = e0 + kCoarseElems < C.E ? kCoarseElems : C.E - e0;
+        for (int q = threadIdx.x; q < ne * P2; q += 256) {
+            switch (C.N) {
+#define SEM_BPC(nn)                                                                                          \
+            case nn:                                                                                         \
+                prolong_column<nn, false, T>(e0 + q / ((nn + 1) * (nn + 1)), q % ((nn + 1) * (nn + 1)), C.evert, \
+                                             C.z0, C.qw, C.inv64, nullptr, zc);                              \
+                break;
+                SEM_BATCH_COARSE_ORDERS(SEM_BPC)
+#undef SEM_BPC
+            }
+        }
+    }
+}
+
+// vertex sums and the Chebyshev start: eight lanes per
+// vertex hold its (up to eight) element corners, added in order
+template <typename T>
+__global__ __launch_bounds__(256) void batch_vert_kernel(const SlotDesc *__restrict__ slots,
+                                                         const CoarseDesc *__restrict__ cd, GroupDev g, int at_start)
+{
+    const int64_t n = g.counts[kCountCoarse + 1];
+    const int sub = threadIdx.x & 7;
+    for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
+        const Item item = g.cv_items[it];
+        const CoarseDesc &C = cd[item.slot];
+        if (coarse_skips<T>(slots[item.slot], at_start)) continue;
+        const int64_t v = (int64_t)item.local * kCoarseRows + (threadIdx.x >> 3);
+        const bool in = v < C.nvert;
+        const int32_t q0 = in ? C.v_off[v] : 0, q1 = in ? C.v_off[v + 1] : 0;
+        const double x = q0 + sub < q1 ? C.partial8[C.v_idx[q0 + sub]] : 0.0;
+        double s = 0.0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const double y = __shfl(x, (threadIdx.x & 56) + c, 64);
+            if (q0 + c < q1) s += y;
+        }
+        if (in && sub == 0) {
+            C.r0[v] = s;
+            C.z0[v] = 0.0;
+            C.res[v] = s;
+            C.d[0][v] = s * C.d0inv[v] * C.inv_theta;
+        }
+    }
+}
+
+// one Chebyshev step (cheb_kernel) of the slots that have a step j
+template <typename T>
+__global__ __launch_bounds__(256) void batch_cheb_kernel(const SlotDesc *__restrict__ slots,
+                                                         const CoarseDesc *__restrict__ cd, GroupDev g, int j,
+                                                         int at_start)
+{
+    const int64_t n = g.counts[kCountCoarse + 1];
+    const int sub = threadIdx.x & 7;
+    for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
+        const Item item = g.cv_items[it];
+        const CoarseDesc &C = cd[item.slot];
+        if (j >= C.k || coarse_skips<T>(slots[item.slot], at_start)) continue;
+        const double *din = C.d[j & 1];
+        const int64_t v = (int64_t)item.local * kCoarseRows + (threadIdx.x >> 3);
+        double s = 0.0;
+        if (v < C.nvert)
+            for (int32_t q = C.a_off[v] + sub; q < C.a_off[v + 1]; q += 8) s += C.a_val[q] * din[C.a_col[q]];
+        s += __shfl_xor(s, 4, 64);
+        s += __shfl_xor(s, 2, 64);
+        s += __shfl_xor(s, 1, 64);
+        double dot = 0.0;
+        if (v < C.nvert && sub == 0) {
+            const double dv = din[v], zv = C.z0[v] + dv, rv = C.res[v] - s;
+            C.z0[v] = zv;
+            C.res[v] = rv;
+            if (j + 1 < C.k) C.d[(j + 1) & 1][v] = C.coef[j] * dv + C.coef[C.k + j] * rv * C.d0inv[v];
+            else dot = C.r0[v] * zv;
+        }
+        if (j + 1 == C.k) {
+            double p[1] = {dot};
+            __syncthreads();
+            block_reduce_store<1>(p, g.cv_partial + it, 0);
+        }
+    }
+}
+
+template <typename T>
+static hipError_t batch_coarse_t(bool at_start, int steps, const SlotDesc *slots, const CoarseDesc *cdesc,
+                                 const GroupDev &g, const BatchLaunch &L, hipStream_t s)
+{
+    const int st = at_start ? 1 : 0;
+    const dim3 grid(L.vec_grid), block(256);
+    hipLaunchKernelGGL(batch_restrict_kernel<T>, grid, block, 0, s, slots, cdesc, g, st);
+    hipLaunchKernelGGL(batch_vert_kernel<T>, grid, block, 0, s, slots, cdesc, g, st);
+    for (int j = 0; j < steps; ++j)
+        hipLaunchKernelGGL(batch_cheb_kernel<T>, grid, block, 0, s, slots, cdesc, g, j, st);
+    hipLaunchKernelGGL(batch_prolong_kernel<T>, grid, block, 0, s, slots, cdesc, g, st);
+    return hipGetLastError();
+}
+
+hipError_t batch_coarse(int prec, bool at_start, int steps, const SlotDesc *slots, const CoarseDesc *cdesc,
+                        const GroupDev &g, const BatchLaunch &L, hipStream_t s)
+{
+    return prec == 0 ? batch_coarse_t<double>(at_start, steps, slots, cdesc, g, L, s)
+                     : batch_coarse_t<float>(at_start, steps, slots, cdesc, g, L, s);
 }
 
 void launch_jacobi(int64_t n, const double *inv, const double *r, double *z, hipStream_t s)

@@ -41,30 +41,22 @@ struct CoarseSpace {
     double *qw = nullptr;       // [2][N+1] 1-D hat weights at the GLL nodes
     int32_t *a_off = nullptr, *a_col = nullptr;  // A0, CSR
     double *a_val = nullptr;
+    double *coef = nullptr;     // [2][k] c1, c2
     double *d0inv = nullptr;    // [nvert] 1/diag(A0), 0 where the vertex is not a coarse unknown
     double *partial8 = nullptr; // [E][8] element restriction sums
     double *r0 = nullptr, *z0 = nullptr, *res = nullptr, *d = nullptr, *tmp = nullptr;
     std::vector<void *> allocations;
 };
 
-// Work vectors of one solve's coarse term: the mesh's own (coarse_work_own,
-// for its single-mesh solves) or a batched slot's, carved from one buffer of
+// Work vectors of one batched slot's coarse term, carved from one buffer of
 // coarse_work_doubles values in this order: element restriction sums [E][8],
-// r0, z0, res, d, tmp [nvert each], the coarse dot's partial pairs and their
-// sum rz (the last two only in carved sets).
+// r0, z0, res, d, tmp [nvert each].  (The mesh's own, for its
+// single-mesh solves, are in CoarseSpace.)
 struct CoarseWork {
-    double *partial8, *r0, *z0, *res, *d, *tmp, *dot, *rz;
+    double *partial8, *r0, *z0, *res, *d, *tmp;
 };
 int64_t coarse_work_doubles(const CoarseSpace *C, int64_t E);
 CoarseWork coarse_work_carve(const CoarseSpace *C, int64_t E, double *base);
-CoarseWork coarse_work_own(const CoarseSpace *C);
-template <typename T>
-void coarse_restrict_w(sem_mesh *m, const CoarseWork &W, const T *r, const T *inv, hipStream_t s);
-int coarse_solve_w(sem_mesh *m, const CoarseWork &W, double *dot_pairs, const PcgState *st, hipStream_t s);
-// z = masked P z0
-void coarse_prolong_w(sem_mesh *m, const CoarseWork &W, double *z, hipStream_t s);
-// z = masked P z0 rounded to FP32 (a mixed-precision batched slot's correction)
-void coarse_prolong_w32(sem_mesh *m, const CoarseWork &W, float *z, hipStream_t s);
 
 // Builds the coarse space of the mesh's current operator (synchronises s).
 CoarseSpace *coarse_build(sem_mesh *m, int k, double frac, hipStream_t s);
