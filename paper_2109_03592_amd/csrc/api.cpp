@@ -79,7 +79,7 @@ static void upload(void *dst, const void *src, size_t bytes, hipStream_t s)
 // waves best (ties: the smaller count), within 150 KB of LDS and a lane
 // budget -- FP64: 512 (256 from N = 10 on, where the kernel runs one wave
 // per SIMD); FP32 (lighter kernels, more waves per SIMD): 256.
-int default_operator_epw(int N, bool fp32)
+static int default_operator_epw(int N, bool fp32)
 {
     const int P2 = (N + 1) * (N + 1), P3 = P2 * (N + 1);
     const int max_lanes = (fp32 || N >= 10) ? 256 : 512;
@@ -97,35 +97,71 @@ int default_operator_epw(int N, bool fp32)
     return best;
 }
 
-// The single-mesh operator from order 8 on runs the plane tile, whose LDS no
-// longer bounds the tile: elements per workgroup measured fastest on pipes of
-// about 10^8 points (CG operator for FP64, plain operator for FP32); beyond
-// order 12 the fullest 64-lane waves.
-static int default_epw(int N, bool fp32 = false)
+// Elements per workgroup of the single-mesh operator's launches at E elements
+// of order N; orders 2 to 12 as measured (boxes of 10^5 to 5*10^7 points, us
+// per launch or per CG iteration, "a: b" for the count not taken: the one
+// taken), beyond order 12 the fullest 64-lane waves.
+static OperatorEpw default_epw(int N, int64_t E)
 {
-    // FP64 N=7: the plane-tile plain operator is fastest at 4 elements per
-    // workgroup, and the CG operator (whole-element tile) runs as fast there
-    if (N == 7 && !fp32) return 4;
-    if (N < 8) return default_operator_epw(N, fp32);
-    static const int f64[] = {3, 1, 2, 3, 3}, f32[] = {3, 5, 2, 3, 3};
-    if (N <= 12) return fp32 ? f32[N - 8] : f64[N - 8];
-    const int P2 = (N + 1) * (N + 1);
-    int best = 1;
-    double best_fill = 0.0;
-    for (int epw = 1; epw * P2 <= 512; ++epw) {
-        const int t = epw * P2, tr = (t + 63) / 64 * 64;
-        if ((double)t / tr > best_fill + 0.005) {
-            best_fill = (double)t / tr;
-            best = epw;
-        }
+    OperatorEpw o;
+    if (N < 2) {
+        o = OperatorEpw::all(default_operator_epw(N, false));
+        o.cg32 = o.plain32 = default_operator_epw(N, true);
+        return o;
     }
-    return best;
+    if (N > 12) {
+        const int P2 = (N + 1) * (N + 1);
+        int best = 1;
+        double best_fill = 0.0;
+        for (int epw = 1; epw * P2 <= 512; ++epw) {
+            const int t = epw * P2, tr = (t + 63) / 64 * 64;
+            if ((double)t / tr > best_fill + 0.005) {
+                best_fill = (double)t / tr;
+                best = epw;
+            }
+        }
+        return OperatorEpw::all(best);
+    }
+    //                            N =  2  3  4  5  6  7  8  9 10 11 12
+    static const int8_t cg[] =      {7, 4, 15, 7, 1, 1, 3, 1, 2, 3, 1};
+    static const int8_t column[] =  {7, 4, 5, 7, 1, 1, 3, 1, 2, 3, 3};
+    static const int8_t plain[] =   {3, 16, 5, 7, 5, 4, 3, 5, 2, 1, 3};
+    static const int8_t helm[] =    {3, 16, 5, 7, 5, 4, 3, 5, 2, 3, 1};
+    static const int8_t cg32[] =    {7, 4, 5, 7, 5, 1, 3, 5, 2, 3, 3};
+    static const int8_t plain32[] = {3, 4, 2, 7, 1, 1, 3, 5, 2, 3, 3};
+    // FP64 CG: N=4 125k elements 694: 632; N=6 32k 423: 414; N=7 27k 422: 406
+    // (with the coarse term 472: 449); N=12 8000 790: 654
+    o.cg = cg[N - 2];
+    o.column = column[N - 2];
+    // FP64 plain: N=2 262k elements 175: 155; N=3 262k 190: 184; N=11 22k 695:
+    // 651; Helmholtz, where the longer tile holds fewer waves, N=12 6859 356: 306
+    o.plain = plain[N - 2];
+    o.helm = helm[N - 2];
+    // FP32 plain: N=2 262k 99: 90; N=4 125k 163: 135; N=6 33k 83: 78
+    o.cg32 = cg32[N - 2];
+    o.plain32 = plain32[N - 2];
+    // N=9 fills five of a workgroup's 512 lanes best, but then a compute unit
+    // holds one workgroup and every barrier stops all of it; the fuller waves
+    // win on large meshes only.  FP64, 4096 elements 71: 57, 50653 694: 690,
+    // 110592 1501 against 1524; FP32 8000 61: 54, 13824 96 against 100
+    if (N == 9 && E < 65536) o.plain = o.helm = 1;
+    if (N == 9 && E < 10240) o.plain32 = 1;
+    // up to four elements per compute unit the work of one workgroup counts,
+    // not the waves: N=9 512 elements 18: 14, N=12 512 38: 30 (FP32 21: 18);
+    // CG N=12 1000 182: 150
+    if (N >= 8 && E <= 1024) o.cg = o.plain = o.helm = o.plain32 = 1;
+    return o;
 }
 
-// FP64 plain operator (modes 0, 1): at N = 9 the plane tile runs 5% faster at
-// five elements per workgroup, where the CG operator loses 2% (it stays at
-// one); elsewhere the two share the setting.
-static int default_plain_epw(int N) { return N == 9 ? 5 : default_epw(N); }
+// Elements per workgroup of a batch's operator launches, before it is tuned:
+// the fullest waves, from order 8 on the single mesh's choice for a few
+// thousand elements
+int default_batch_epw(int N, bool fp32)
+{
+    if (N < 8 || N > 12) return default_operator_epw(N, fp32);
+    const OperatorEpw o = default_epw(N, 4096);
+    return fp32 ? o.plain32 : o.cg;
+}
 
 // Derivative matrices of every order in the kernels' constant table, once
 // per device.
@@ -231,19 +267,6 @@ struct Prec<float> {
     static const float *h2b(sem_mesh *m) { return m->helm ? m->h2b32 : nullptr; }
 };
 
-// elements per workgroup of the operator kernel in use for precision T
-template <typename T>
-static int op_epw(const sem_mesh *m)
-{
-    return sizeof(T) == 8 ? m->ax_epw : m->ax_epw32;
-}
-// ... of the plain operator (modes 0, 1)
-template <typename T>
-static int plain_epw(const sem_mesh *m)
-{
-    return sizeof(T) == 8 ? m->ax_epw_plain : m->ax_epw32;
-}
-
 // the CG iteration of precision T adds the coarse correction
 template <typename T>
 static bool coarse_cg(const sem_mesh *m) { return m->coarse != nullptr; }
@@ -256,13 +279,15 @@ static bool schwarz_cg(const sem_mesh *m) { return sizeof(T) == 8 && m->schwarz 
 template <typename T>
 static int cg_mode(const sem_mesh *m) { return (schwarz_cg<T>(m) ? 4 : 2) + (coarse_cg<T>(m) ? 1 : 0); }
 
-// elements per workgroup of the column kernel for precision T
+// elements per workgroup of the operator launch of a mode
 template <typename T>
-static int column_epw(const sem_mesh *m) { return sizeof(T) == 8 ? m->ax_epw : m->ax_epw32; }
-
-// elements per workgroup of the CG operator launch (modes 3-5 run the column kernel)
-template <typename T>
-static int cg_epw(const sem_mesh *m) { return cg_mode<T>(m) > 2 ? column_epw<T>(m) : op_epw<T>(m); }
+static int op_epw(const sem_mesh *m, int mode)
+{
+    const OperatorEpw &o = m->epw;
+    if (sizeof(T) == 4) return mode <= 1 ? o.plain32 : o.cg32;
+    if (mode <= 1) return m->helm ? o.helm : o.plain;
+    return mode == 2 ? o.cg : o.column;
+}
 
 // launches the operator; returns its workgroup count (the number of dot
 // partials of modes 1-5)
@@ -271,7 +296,7 @@ static AxParams<T> ax_params(sem_mesh *m, int mode, const T *in, T *out)
 {
     AxParams<T> a{};
     a.E = m->h.E;
-    a.epw = mode >= 3 ? column_epw<T>(m) : (mode <= 1 ? plain_epw<T>(m) : op_epw<T>(m));
+    a.epw = op_epw<T>(m, mode);
     a.grid_cap = m->ax_grid_cap;
     a.G = Prec<T>::G(m);
     a.in = in;
@@ -598,7 +623,7 @@ static void run_iterations(sem_mesh *m, int k, bool use_graph, hipStream_t s, Pr
     }
     const int slot = sizeof(T) == 8 ? 0 : 1;
     // graph key: tile shape and kernel (a change of the coarse space drops the graphs)
-    const int epw = cg_epw<T>(m) + 1024 * (coarse_cg<T>(m) ? 2 : 0);
+    const int epw = op_epw<T>(m, cg_mode<T>(m)) + 1024 * (coarse_cg<T>(m) ? 2 : 0);
     if (!m->graph[slot] || m->graph_k[slot] != k || m->graph_epw[slot] != epw ||
         m->graph_grid[slot] != m->ax_grid_cap) {
         if (m->graph[slot]) {
@@ -1064,9 +1089,7 @@ sem_status sem_setup(const sem_mesh_desc *desc, void *stream, sem_mesh **out)
             SEM_HIP(hipGetDevice(&m->device));
             init_scratch(m->device);
             m->with_fp32 = (desc->precision_flags & SEM_WITH_FP32) ? 1 : 0;
-            m->ax_epw = default_epw(h.N);
-            m->ax_epw32 = default_epw(h.N, true);
-            m->ax_epw_plain = default_plain_epw(h.N);
+            m->epw = default_epw(h.N, h.E);
             m->axgs = new AxgsSpace();
             const int64_t nL = h.nL;
             ensure_dtables(s);
@@ -1317,9 +1340,7 @@ sem_status sem_set_operator_config(sem_mesh *m, int epw, int grid)
         if (grid < 0) fail(SEM_EINVAL, "sem_set_operator_config: negative grid");
         const int cap = grid > 0 ? grid : persistent_grid_cap();
         if (cap > m->n_partials - 64) fail(SEM_EINVAL, "sem_set_operator_config: grid larger than the partials buffer");
-        m->ax_epw = epw;
-        m->ax_epw32 = epw;
-        m->ax_epw_plain = epw;
+        m->epw = OperatorEpw::all(epw);
         m->ax_grid_cap = cap;
         return SEM_OK;
     });
@@ -1329,7 +1350,7 @@ sem_status sem_get_operator_config(const sem_mesh *m, int *epw, int *grid)
 {
     return guarded([&]() -> sem_status {
         if (!m) fail(SEM_EINVAL, "sem_get_operator_config: null mesh");
-        if (epw) *epw = m->ax_epw;
+        if (epw) *epw = m->epw.cg;
         if (grid) *grid = m->ax_grid_cap;
         return SEM_OK;
     });
@@ -1440,7 +1461,7 @@ sem_status sem_ax_noalloc(sem_mesh *m, int dtype, const void *u, void *w, double
         double *part = scratch_of(dev);
         if (!part) fail(SEM_EHIP, "sem_ax_noalloc: no scratch address for this device");
         // the operator launches min(tiles, grid cap) workgroups, one partial each
-        const int epw = dtype == SEM_FP64 ? op_epw<double>(m) : op_epw<float>(m);
+        const int epw = dtype == SEM_FP64 ? op_epw<double>(m, 1) : op_epw<float>(m, 1);
         const int64_t tiles = (m->h.E + epw - 1) / epw;
         const int64_t grid = std::min<int64_t>(tiles, m->ax_grid_cap);
         if (grid > kNoallocPartials)

@@ -148,12 +148,11 @@ static void *balloc(sem_batch *B, size_t bytes)
     return p;
 }
 
-// elements per operator tile: the single-mesh rule (fill whole waves)
-int default_operator_epw(int N, bool fp32);
+int default_batch_epw(int N, bool fp32);  // api.cpp
 
 static int batch_epw(const sem_batch *B, int N, int prec)
 {
-    return B->epw[prec][N] > 0 ? B->epw[prec][N] : default_operator_epw(N, prec == 1);
+    return B->epw[prec][N] > 0 ? B->epw[prec][N] : default_batch_epw(N, prec == 1);
 }
 
 static void group_alloc(sem_batch *B, Group &g, int prec)
@@ -1014,7 +1013,7 @@ sem_status sem_batch_tune(sem_batch *B, sem_mesh *const *meshes, int n, void *st
                     int emax = (N >= 10 ? 256 : 512) / P2;
                     while (emax > 1 && (size_t)3 * emax * P3 * sizeof(double) > 150 * 1024) --emax;
                     double best = 1e300;
-                    int best_e = default_operator_epw(N, prec == 1);
+                    int best_e = default_batch_epw(N, prec == 1);
                     for (int e = 1; e <= emax; ++e) {
                         if (emax > 8 && e != 1 && e != emax && (e & (e - 1)) != 0 && e != best_e) continue;
                         B->epw[prec][N] = e;

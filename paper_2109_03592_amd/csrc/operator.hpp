@@ -453,18 +453,30 @@ __device__ inline void ax_tile_planes(const LaneRows<T, N> &R, const T *__restri
     T acc[P];
 #pragma unroll
     for (int k = 0; k < P; ++k) acc[k] = 0;
-    // the factors of plane k + 1 are loaded while plane k is worked on, so
-    // that their latency overlaps a whole plane's barriers and LDS products
-    T gn[6];
+    // the factors of plane k + 1 (HELM: and its h1 and h2 B) are loaded while
+    // plane k is worked on, so that their latency overlaps a whole plane's
+    // barriers and LDS products.  h1 loaded where it multiplies, and h2 B after
+    // the last plane, cost the Helmholtz operator one latency per plane: N = 9,
+    // 13.8M points 270 -> 228 us (floor 178), N = 12 385 -> 295 us.  A second
+    // plane ahead gains nothing more (N = 9: 232 us) and takes registers.
+    T gn[6], hn = 0, bn = 0;
 #pragma unroll
     for (int c = 0; c < 6; ++c) gn[c] = active ? ld_stream(Ge + c * P3) : T(0);
+    if (HELM && active) {
+        hn = ld_stream(h1 + eb + ij);
+        bn = ld_stream(h2b + eb + ij);
+    }
 #pragma unroll 1
     for (int k = 0; k < P; ++k) {
-        const T g1 = gn[0], g2 = gn[1], g3 = gn[2], g4 = gn[3], g5 = gn[4], g6 = gn[5];
+        const T g1 = gn[0], g2 = gn[1], g3 = gn[2], g4 = gn[3], g5 = gn[4], g6 = gn[5], h = hn, b = bn;
         if (active && k + 1 < P) {
             const T *g = Ge + (k + 1) * P2;
 #pragma unroll
             for (int c = 0; c < 6; ++c) gn[c] = ld_stream(g + c * P3);
+            if (HELM) {
+                hn = ld_stream(h1 + eb + ij + (k + 1) * P2);
+                bn = ld_stream(h2b + eb + ij + (k + 1) * P2);
+            }
         }
         T uk = uc[0];
 #pragma unroll
@@ -482,7 +494,6 @@ __device__ inline void ax_tile_planes(const LaneRows<T, N> &R, const T *__restri
         T ws = g2 * us + g4 * ur + g6 * ut;
         T wt = g3 * ut + g5 * ur + g6 * us;
         if (HELM) {
-            const T h = active ? ld_stream(h1 + eb + ij + k * P2) : T(0);
             wr *= h;
             ws *= h;
             wt *= h;
@@ -492,7 +503,7 @@ __device__ inline void ax_tile_planes(const LaneRows<T, N> &R, const T *__restri
             ss[ij] = ws;
         }
         __syncthreads();
-        T a = 0;
+        T a = HELM ? b * uk : T(0);
 #pragma unroll
         for (int l = 0; l < P; ++l) a += R.dti(l) * sr[j * P + l] + R.dtj(l) * ss[l * P + i];
         // D^T in t: plane k's flux reaches every output plane kk with D[k][kk]
@@ -502,8 +513,7 @@ __device__ inline void ax_tile_planes(const LaneRows<T, N> &R, const T *__restri
     constexpr bool kSink = !std::is_same<Sink, NoSink>::value;
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-        T v = acc[k];
-        if (HELM && active) v += ld_stream(h2b + eb + ij + k * P2) * uc[k];
+        const T v = acc[k];
         if constexpr (kSink) sink(k, v);
         else if (active) st_stream(v, out + eb + ij + k * P2);
         if (MODE != 0) dot += (double)uc[k] * (double)v;

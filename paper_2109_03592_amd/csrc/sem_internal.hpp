@@ -84,6 +84,14 @@ struct DeviceBuf {
     size_t bytes = 0;
 };
 
+// Elements per workgroup of the operator launches: FP64 CG (mode 2), FP64 CG
+// with the coarse term or the Schwarz solves (modes 3-5), FP64 plain (modes 0,
+// 1), the same in the Helmholtz form, FP32 CG, FP32 plain.
+struct OperatorEpw {
+    int cg = 1, column = 1, plain = 1, helm = 1, cg32 = 1, plain32 = 1;
+    static OperatorEpw all(int epw) { return {epw, epw, epw, epw, epw, epw}; }
+};
+
 struct CoarseSpace;   // coarse.hpp
 struct SchwarzSpace;  // schwarz.hpp
 struct AxgsSpace;     // axgs_host.hpp
@@ -134,9 +142,7 @@ struct sem_mesh {
     int64_t n_partials = 0;
     sem::PcgState *state = nullptr;  // [2]: FP64 solve, FP32 inner solve
     double *scal = nullptr;          // small device scratch for norms
-    int ax_epw = 1;                  // elements per workgroup of the FP64 operator
-    int ax_epw32 = 1;                // ... of the FP32 operator
-    int ax_epw_plain = 1;            // ... of the FP64 plain operator (modes 0, 1)
+    sem::OperatorEpw epw;            // elements per workgroup of the operator launches
     int ax_grid_cap = 4096;          // persistent operator grid
     std::vector<hipEvent_t> events;  // profiling event pool
     hipStream_t capture_stream = nullptr;
