@@ -135,8 +135,6 @@ __global__ __launch_bounds__(kBatchBlock) void batch_gs_kernel(const SlotDesc *s
     }
 }
 
-__device__ inline double inv_mult_b(uint8_t m) { return 1.0 / (double)m; }
-
 // CG update after the gather-scatter: r -= alpha w; per-item partials of
 // <r,r>, <r, invdiag r>.  The x step is applied by the next operator launch.
 template <typename T>
@@ -175,7 +173,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_update_kernel(const SlotDes
                 if (q > qlast) break;
                 const T rq = rv[u] - alpha * wv[u];
                 st_stream(rq, r + q);
-                const double rd = (double)rq, im = inv_mult_b(mv[u]);
+                const double rd = (double)rq, im = inv_mult(mv[u]);
                 rr += rd * rd * im;
                 rz += rd * (double)(ivv[u] * rq) * im;
             }
@@ -206,7 +204,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_init_kernel(const SlotDesc 
             const int64_t q = q0 + u * kBatchBlock + threadIdx.x;
             if (q >= sd.nL) break;
             p[q] = T(0);
-            const double rd = (double)r[q], im = inv_mult_b(sd.mult[q]);
+            const double rd = (double)r[q], im = inv_mult(sd.mult[q]);
             rr += rd * rd * im;
             rz += rd * (double)(iv[q] * r[q]) * im;
         }
@@ -241,7 +239,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_residual_kernel(const SlotD
                 rq = bq - w[q];
             }
             r[q] = rq;
-            const double im = inv_mult_b(sd.mult[q]);
+            const double im = inv_mult(sd.mult[q]);
             rr += rq * rq * im;
             bb += bq * bq * im;
         }

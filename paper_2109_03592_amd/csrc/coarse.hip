@@ -72,13 +72,6 @@ __device__ inline double wave_sum8(const double (&s)[8])
     return v;
 }
 
-// 1/mult exactly: a node's copies are one or two along each axis, so its
-// multiplicity is a power of two and the reciprocal only sets an exponent
-__device__ inline double inv_mult_c(uint8_t m)
-{
-    return __longlong_as_double((long long)(1023 - __builtin_ctz(m)) << 52);
-}
-
 // E8[e][c'][c] = sum over element e's live nodes of phi_c' * w, w = A_e u_c
 __global__ __launch_bounds__(256) void elem_coarse_kernel(int64_t E, int P, const double *__restrict__ w,
                                                           const double *__restrict__ qw,
@@ -131,7 +124,7 @@ __device__ inline void restrict_element(int64_t e, const T *__restrict__ r, cons
 #pragma unroll
     for (int q = lane; q < P3; q += 64) {
         const T iv = ld_stream(inv + base + q);
-        const double v = iv > T(0) ? (double)ld_stream(r + base + q) * inv_mult_c(ld_stream(mult + base + q)) : 0.0;
+        const double v = iv > T(0) ? (double)ld_stream(r + base + q) * inv_mult(ld_stream(mult + base + q)) : 0.0;
         hat_add<N>(sqw, q, v, s);
     }
     const double out = wave_sum8(s);
@@ -192,7 +185,7 @@ __global__ __launch_bounds__(256) void update_restrict_kernel(int64_t E, const P
                 rv.x = rv.x - (float)alpha * wv.x;
                 rv.y = rv.y - (float)alpha * wv.y;
                 st_stream(rv, reinterpret_cast<float2 *>(r + base) + h);
-                const double ima = inv_mult_c((uint8_t)(mm & 0xff)), imb = inv_mult_c((uint8_t)(mm >> 8));
+                const double ima = inv_mult((uint8_t)(mm & 0xff)), imb = inv_mult((uint8_t)(mm >> 8));
                 const double ra = (double)rv.x, rb = (double)rv.y;
                 rr += ra * ra * ima;
                 rr += rb * rb * imb;
@@ -210,7 +203,7 @@ __global__ __launch_bounds__(256) void update_restrict_kernel(int64_t E, const P
                 const T rv = ld_stream(r + o) - alpha * ld_stream(w + o);
                 st_stream(rv, r + o);
                 const T iv = ld_stream(inv + o);
-                const double im = inv_mult_c(ld_stream(mult + o));
+                const double im = inv_mult(ld_stream(mult + o));
                 const double rd = (double)rv;
                 rr += rd * rd * im;
                 if (with_rz) rz += rd * (double)(iv * rv) * im;

@@ -198,8 +198,6 @@ __global__ void fp64_to_fp32_kernel(int64_t n, const double *__restrict__ a, flo
         out[q] = (float)a[q];
 }
 
-__device__ inline double inv_mult(uint8_t m) { return 1.0 / (double)m; }
-
 // partial of sum a*b/mult (unique-dof inner product)
 template <typename T>
 __global__ __launch_bounds__(256) void dot_unique_kernel(int64_t n, const T *__restrict__ a, const T *__restrict__ b,

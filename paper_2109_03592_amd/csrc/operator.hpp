@@ -36,6 +36,13 @@ __device__ inline void block_reduce_store(double (&v)[NV], double *dst, int stri
     }
 }
 
+// 1/mult exactly: a node's copies are one or two along each axis, so its
+// multiplicity is a power of two and the reciprocal only sets an exponent
+__device__ inline double inv_mult(uint8_t m)
+{
+    return __longlong_as_double((long long)(1023 - __builtin_ctz(m)) << 52);
+}
+
 // ---------------------------------------------------------------------------
 // Streaming accesses: data read or written once per launch bypass the caches
 // (non-temporal), which keeps them from evicting what is reused.
