@@ -384,9 +384,9 @@ sem_status sem_pcg_solve(sem_mesh *mesh, const double *b, double *x, const sem_s
  * the rounded correction.  Batched solves (sem_batch_*): a slot of a mesh
  * with a coarse space takes the coarse term too, in its CG (FP64, or the
  * FP32 inner iterations of a mixed slot), with its own coarse vectors
- * (several slots may share the mesh) -- its restriction, Chebyshev solve
- * (FP64) and prolongation P z0 (rounded to the CG's precision) run per slot
- * after the batched update, and the batched operator adds P z0 in its p
+ * (several slots may share the mesh) -- the restriction, Chebyshev solve
+ * (FP64) and prolongation P z0 (rounded to the CG's precision) of all slots
+ * run after the batched update, and the batched operator adds P z0 in its p
  * update, so the preconditioner is the same M (prolongation summed in
  * another order: the same to rounding).  The coarse space must not change
  * (sem_set_coarse) while the mesh has slots in a batch.
@@ -504,8 +504,8 @@ sem_status sem_proj_solve(sem_proj *proj, const double *b, double *x, const sem_
  * products are summed from its own items in a fixed order, so a slot's result
  * does not depend on which other slots share the launches.  The
  * preconditioner is Jacobi, plus the coarse term of Eq. 6 for the slots of
- * a mesh with a coarse space (sem_set_coarse; its per-slot phases are
- * launched slot by slot); meshes with the Helmholtz form or the Schwarz local
+ * a mesh with a coarse space (sem_set_coarse; each phase one launch over all
+ * of them); meshes with the Helmholtz form or the Schwarz local
  * solves are refused (SEM_EUNSUPPORTED).
  *
  * Ownership: the batch owns its slot vectors (allocated within

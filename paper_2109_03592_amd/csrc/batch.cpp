@@ -256,7 +256,7 @@ static void group_build(sem_batch *B, Group &g, const std::vector<int> &ids, hip
         g.h_vc[id] = nv;
         for (int64_t t = 0; t < nv; ++t) g.h_vec.push_back(Item{id, (int32_t)t});
     }
-    // the coarse term: element and vertex items of every slot that takes it
+    // the coarse term: element and tile items of every slot that takes it
     g.h_ce.clear();
     g.h_cv.clear();
     g.h_cvf.assign(B->max_slots, 0);
@@ -267,11 +267,11 @@ static void group_build(sem_batch *B, Group &g, const std::vector<int> &ids, hip
         const CoarseDesc &c = B->h_cdesc[id];
         const int64_t ne = (c.E + kCoarseElems - 1) / kCoarseElems;
         for (int64_t t = 0; t < ne; ++t) g.h_ce.push_back(Item{id, (int32_t)t});
-        const int64_t nv = (c.nvert + kCoarseRows - 1) / kCoarseRows;
+        const int64_t nv = c.chain.tiles.n;
         g.h_cvf[id] = (int64_t)g.h_cv.size();
         g.h_cvc[id] = nv;
         for (int64_t t = 0; t < nv; ++t) g.h_cv.push_back(Item{id, (int32_t)t});
-        g.coarse_steps = std::max(g.coarse_steps, c.k);
+        g.coarse_steps = std::max(g.coarse_steps, c.chain.k);
     }
     group_reserve(B, g, std::max<size_t>(g.h_ax.size(), 1), std::max<size_t>(g.h_gs.size(), 1),
                   std::max<size_t>(g.h_vec.size(), 1), std::max<size_t>(g.h_ce.size(), 1),
@@ -731,26 +731,13 @@ static int admit_slot(sem_batch *B, sem_mesh *m, const double *b, double *x, con
         CoarseDesc &c = B->h_cdesc[id];
         c = CoarseDesc();
         c.N = hm.N;
-        c.k = C->k;
         c.E = hm.E;
-        c.nvert = C->nvert;
-        c.inv_theta = C->inv_theta;
         c.evert = C->evert;
-        c.v_off = C->v_off;
-        c.v_idx = C->v_idx;
-        c.a_off = C->a_off;
-        c.a_col = C->a_col;
-        c.a_val = C->a_val;
-        c.d0inv = C->d0inv;
         c.qw = C->qw;
-        c.coef = C->coef;
         c.inv64 = m->inv64;
         c.partial8 = h.cw.partial8;
-        c.r0 = h.cw.r0;
         c.z0 = h.cw.z0;
-        c.res = h.cw.res;
-        c.d[0] = h.cw.d;
-        c.d[1] = h.cw.tmp;
+        c.chain = coarse_chain(C, h.cw);
         SEM_HIP(hipMemcpyAsync(B->d_cdesc + id, &c, sizeof(CoarseDesc), hipMemcpyHostToDevice, s));
     }
     SEM_HIP(hipMemsetAsync(d.st, 0, 2 * sizeof(PcgState), s));

@@ -13,6 +13,7 @@
 
 #include <cstdint>
 
+#include "coarse.hpp"
 #include "sem_internal.hpp"
 
 namespace sem {
@@ -21,10 +22,9 @@ constexpr int kBatchBlock = 256;       // threads per workgroup of every batched
 constexpr int kGsChunk = 256;          // gather-scatter ids per item
 constexpr int kVecChunk = 256 * 8;     // vector points per item
 // coarse items: elements of the restriction and prolongation (one per
-// wavefront; 16 of them in turn took 32 us where four at once take 8) and
-// vertices, eight lanes each
+// wavefront; 16 of them in turn took 32 us where four at once take 8); the
+// vertex items are the tiles of coarse.hpp
 constexpr int kCoarseElems = 4;
-constexpr int kCoarseRows = 32;
 
 struct Item {
     int32_t slot;
@@ -63,20 +63,19 @@ struct SlotDesc {
 // The coarse term of one slot (csrc/coarse.hpp), for the batched coarse
 // kernels: its mesh's coarse space and its own work vectors.
 struct CoarseDesc {
-    int N, k;             // order, Chebyshev steps
-    int64_t E, nvert;
-    double inv_theta;
-    const int32_t *evert, *v_off, *v_idx, *a_off, *a_col;
-    const double *a_val, *d0inv, *qw, *coef;  // coef: [k] c1, [k] c2
-    const double *inv64;
-    double *partial8, *r0, *z0, *res, *d[2];
+    int N;
+    int64_t E;
+    const int32_t *evert;
+    const double *qw, *inv64;
+    double *partial8, *z0;
+    CoarseChain chain;
 };
 
 // counts[] of a group: [0] n_slots, [1] ax items, [2] gs items, [3] vec
 // items, then per order N the operator items' [first, count] at
 // kCountAxRange + 2N (operator items are sorted by order, then slot)
 constexpr int kCountAxRange = 4;
-// coarse slots' element items, vertex items
+// coarse slots' element items, tile items
 constexpr int kCountCoarse = kCountAxRange + 2 * (SEM_MAX_ORDER + 1);
 constexpr int kCountSize = kCountCoarse + 2;
 
@@ -91,7 +90,7 @@ struct GroupDev {
     const int64_t *vec_count;
     double *ax_partial;       // per ax item
     double *vec_partial;      // 2 per vec item
-    const Item *ce_items, *cv_items;  // coarse: element chunks, vertex chunks
+    const Item *ce_items, *cv_items;  // coarse: element chunks, vertex tiles
     const int64_t *cv_first, *cv_count;
     double *cv_partial;       // per cv item: its share of r0.z0
 };

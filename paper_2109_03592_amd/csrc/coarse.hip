@@ -17,12 +17,14 @@
 // Dirichlet nodes are the nodes whose inverse diagonal is 0.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
 #include "batch.hpp"
 #include "coarse.hpp"
 #include "kernels.hpp"
+#include "lattice.hpp"
 #include "operator.hpp"
 
 namespace sem {
@@ -217,67 +219,160 @@ __global__ __launch_bounds__(256) void update_restrict_kernel(int64_t E, const P
     block_reduce_store<2>(v, partial, 2);
 }
 
-// r0[v] = sum of v's element corners (ascending element, corner); then the
-// Chebyshev start: z = 0, res = r0, d = D0^-1 r0 / theta
-__global__ __launch_bounds__(256) void restrict_vert_kernel(int64_t nv, const int32_t *__restrict__ v_off,
-                                                            const int32_t *__restrict__ v_idx,
-                                                            const double *__restrict__ partial8,
-                                                            const double *__restrict__ d0inv, double inv_theta,
-                                                            double *__restrict__ r0, double *__restrict__ z,
-                                                            double *__restrict__ res, double *__restrict__ d,
-                                                            const PcgState *__restrict__ st)
+// sum over eight lanes: pairs, fours, the other four, on the vector unit
+__device__ inline double sum8(double v)
 {
-    if (st && st->done) return;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x) {
-        double s = 0.0;
-        for (int32_t q = v_off[v]; q < v_off[v + 1]; ++q) s += partial8[v_idx[q]];
-        r0[v] = s;
-        z[v] = 0.0;
-        res[v] = s;
-        d[v] = s * d0inv[v] * inv_theta;
-    }
+    auto moved = [](double x, auto ctrl) {
+        constexpr int kCtrl = decltype(ctrl)::value;
+        const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), kCtrl, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kCtrl, 0xf, 0xf, true);
+        return __hiloint2double(hi, lo);
+    };
+    v += moved(v, std::integral_constant<int, 0xB1>());   // quad_perm 1,0,3,2
+    v += moved(v, std::integral_constant<int, 0x4E>());   // quad_perm 2,3,0,1
+    v += moved(v, std::integral_constant<int, 0x141>());  // row_half_mirror
+    return v;
 }
 
-// One Chebyshev step, eight lanes per row of A0 (its entries read
-// contiguously, summed by a fixed butterfly):
-//   z += d_in; res -= A0 d_in; d_out = c1 d_in + c2 D0^-1 res.
-// LAST: no d_out; (0, sum r0 z) pairs per workgroup into `partial` when given.
-template <bool LAST>
-__global__ __launch_bounds__(256) void cheb_kernel(int64_t nv, const int32_t *__restrict__ off,
-                                                   const int32_t *__restrict__ col, const double *__restrict__ val,
-                                                   double c1, double c2, const double *__restrict__ d0inv,
-                                                   const double *__restrict__ din, double *__restrict__ dout,
-                                                   double *__restrict__ z, double *__restrict__ res,
-                                                   const double *__restrict__ r0, double *__restrict__ partial,
-                                                   const PcgState *__restrict__ st)
+// One launch of the Chebyshev solve A0 z = r0, for one tile: up to kTileSteps
+// of the steps z += d; res -= A0 d; d = c1 d + c2 D0^-1 res.  The last step
+// needs its z only, so the step before it adds that d too and k steps are
+// k - 1 products.  The first launch starts from the element sums: r0[v] the sum
+// of v's element corners (ascending), z = 0, res = r0, d = D0^-1 r0 / theta.
+// Later launches read res and d around the box from buffers their own results
+// do not go to.  A row's entries are taken by eight lanes and summed by a
+// fixed pattern.  Returns this lane's part of sum r0 z at the end.
+//
+// On a mesh of a few thousand elements each step as a launch of its own costs
+// the 4.5 us of any small kernel and does next to nothing.  A tile's launch is
+// bound by its lookups (listed vertices' corners, rows around the box), which
+// is why it repeats work on small boxes rather than less on few large ones.
+// 16x16x16 pipe, 4 steps (216 tiles): 24 us in five launches -> 12 us in one;
+// 24x24x48, 192 tiles of a larger edge: 30 -> 23 us; the 12 boxes of a batch
+// (up to 1024 elements): 19 -> 7 us.  Rows kept in registers from step to step
+// were no faster, and shuffles through the LDS instead of sum8 0.5 us slower.
+__device__ inline double coarse_tile(const CoarseChain &C, int t, int launch, double *sm)
 {
-    if (st && st->done) return;
-    const int sub = threadIdx.x & 7;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    double dot = 0.0;
-    // wave-uniform trip count: the butterfly runs on full wavefronts
-    for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63); t0 < nv * 8; t0 += stride) {
-        const int64_t v = (t0 + (threadIdx.x & 63)) >> 3;
-        double s = 0.0;
-        if (v < nv)
-            for (int32_t q = off[v] + sub; q < off[v + 1]; q += 8) s += val[q] * din[col[q]];
-        s += __shfl_xor(s, 4, 64);
-        s += __shfl_xor(s, 2, 64);
-        s += __shfl_xor(s, 1, 64);
-        if (v < nv && sub == 0) {
-            const double dv = din[v];
-            const double zv = z[v] + dv;
-            z[v] = zv;
-            const double rv = res[v] - s;
-            res[v] = rv;
-            if (!LAST) dout[v] = c1 * dv + c2 * rv * d0inv[v];
-            else dot += r0[v] * zv;
+    const CoarseTiles &T = C.tiles;
+    double *da = sm, *db = da + kTileVerts, *res = db + kTileVerts, *dinv = res + kTileRows, *z = dinv + kTileRows;
+    double *r0 = z + kTileCore;
+    int32_t *verts = reinterpret_cast<int32_t *>(r0 + kTileCore);
+    const int j0 = launch * kTileSteps;
+    const int left = C.k - 1 - j0, steps = left < kTileSteps ? left : kTileSteps;
+    const bool first = launch == 0, last = left <= kTileSteps;
+    const int tid = threadIdx.x, sub = tid & 7;
+    const int64_t vbase = (int64_t)t * T.verts, rbase = (int64_t)t * T.rows;
+    const int4 lv = reinterpret_cast<const int4 *>(T.level)[t];
+    const int level[kTileSteps + 1] = {lv.x, lv.y, lv.z, lv.w};
+    double c1[kTileSteps], c2[kTileSteps];
+#pragma unroll
+    for (int q = 0; q < kTileSteps; ++q) {
+        c1[q] = q < steps ? C.coef[j0 + q] : 0.0;
+        c2[q] = q < steps ? C.coef[C.k + j0 + q] : 0.0;
+    }
+    const double *din = C.d[launch & 1], *rin = C.res[launch & 1];
+    for (int h = tid; h < T.verts; h += kTileThreads) {
+        const int v = T.vert[vbase + h];
+        const double di = C.d0inv[v];
+        double d, r = 0.0, sum = 0.0;
+        if (first || (last && h < T.core)) {
+            int32_t idx[8];
+            double y[8];
+            const int4 *cn = reinterpret_cast<const int4 *>(T.corner + (vbase + h) * 8);
+            const int4 ca = cn[0], cb = cn[1];
+            idx[0] = ca.x; idx[1] = ca.y; idx[2] = ca.z; idx[3] = ca.w;
+            idx[4] = cb.x; idx[5] = cb.y; idx[6] = cb.z; idx[7] = cb.w;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) y[c] = idx[c] >= 0 ? C.partial8[idx[c]] : 0.0;
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if (idx[c] >= 0) sum += y[c];
+        }
+        if (first) {
+            r = sum;
+            d = sum * di * C.inv_theta;
+        } else {
+            d = din[v];
+            if (h < T.rows) r = rin[v];
+        }
+        da[h] = d;
+        if (h < T.rows) {
+            res[h] = r;
+            dinv[h] = di;
+            verts[h] = v;
+        }
+        if (h < T.core) {
+            z[h] = first ? 0.0 : C.z0[v];
+            r0[h] = sum;
         }
     }
-    if (LAST && partial) {
-        double p[2] = {0.0, dot};
-        block_reduce_store<2>(p, partial, 2);
+    __syncthreads();
+    const int nc = level[0];
+    for (int q = 0; q < steps; ++q) {
+        const bool end = last && q == steps - 1;
+        const int left_rows = steps - 1 - q;
+        const int n = left_rows == 2 ? level[2] : (left_rows == 1 ? level[1] : level[0]);
+        const double e1 = q == 0 ? c1[0] : (q == 1 ? c1[1] : c1[2]), e2 = q == 0 ? c2[0] : (q == 1 ? c2[1] : c2[2]);
+        // wave-uniform trip count: the sums run on full wavefronts
+#pragma unroll 2
+        for (int h0 = (tid >> 6) * 8; h0 < n; h0 += kTileThreads / 8) {
+            const int h = h0 + ((tid & 63) >> 3);
+            double s = 0.0;
+            if (h < n) {
+                const double2 *val = reinterpret_cast<const double2 *>(C.a_val + ((int64_t)verts[h] * 8 + sub) * 4);
+                const double2 va = val[0], vb = val[1];
+                const short4 c = reinterpret_cast<const short4 *>(T.col)[(rbase + h) * 8 + sub];
+                if (c.x >= 0) s += va.x * da[c.x];
+                if (c.y >= 0) s += va.y * da[c.y];
+                if (c.z >= 0) s += vb.x * da[c.z];
+                if (c.w >= 0) s += vb.y * da[c.w];
+            }
+            s = sum8(s);
+            if (h < n && sub == 0) {
+                const double dv = da[h], rv = res[h] - s, dn = e1 * dv + e2 * rv * dinv[h];
+                res[h] = rv;
+                db[h] = dn;
+                if (h < nc) {
+                    const double zv = z[h] + dv;
+                    z[h] = end ? zv + dn : zv;
+                }
+            }
+        }
+        __syncthreads();
+        double *x = da;
+        da = db;
+        db = x;
     }
+    double dot = 0.0;
+    for (int h = tid; h < nc; h += kTileThreads) {
+        const int v = T.vert[vbase + h];
+        const double zv = steps == 0 ? z[h] + da[h] : z[h];
+        C.z0[v] = zv;
+        if (last) {
+            dot += r0[h] * zv;
+        } else {
+            C.d[(launch + 1) & 1][v] = da[h];
+            C.res[(launch + 1) & 1][v] = res[h];
+        }
+    }
+    __syncthreads();  // the next tile rewrites the LDS
+    return dot;
+}
+
+// Chebyshev launch `launch` of a mesh; in the last one the (0, sum r0 z) pair
+// of each workgroup goes into `partial` when given.
+__global__ __launch_bounds__(kTileThreads) void coarse_tile_kernel(CoarseChain C, int launch,
+                                                                   double *__restrict__ partial,
+                                                                   const PcgState *__restrict__ st)
+{
+    if (st && st->done) return;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    double p[2] = {0.0, 0.0};
+    // the workgroups of one XCD take neighbouring tiles, whose rows overlap
+    const XcdRange X = xcd_range(C.tiles.n);
+    for (int64_t t = X.first; t < X.hi; t += X.step)
+        p[1] += coarse_tile(C, (int)t, launch, reinterpret_cast<double *>(smem_raw));
+    if (partial) block_reduce_store<2>(p, partial, 2);
 }
 
 // z = masked P z0, or with r z = inv r + masked P z0 (the whole
@@ -360,6 +455,89 @@ void coarse_free(CoarseSpace *C)
     delete C;
 }
 
+// The tiles of the vertex lattice (extents vd).  The box edge is the smallest
+// from 3 on that gives at most a workgroup per compute unit: a smaller box
+// lists fewer vertices, which is what a workgroup's time goes by, a larger one
+// repeats less (3: 27 listed vertices per vertex, 8: 5.4).  Preconditioner of
+// 16^3 elements with edge 2, 3 and 4: 31.0, 31.0 and 32.8 us.
+static void build_tiles(CoarseSpace *C, const int vd[3], const std::vector<int32_t> &v_off,
+                        const std::vector<int32_t> &v_idx, const std::vector<int32_t> &off,
+                        const std::vector<int32_t> &col, hipStream_t s)
+{
+    int nt[3];
+    for (int edge = 3; edge <= kTileEdge; ++edge) {
+        for (int a = 0; a < 3; ++a) nt[a] = (vd[a] + edge - 1) / edge;
+        if ((int64_t)nt[0] * nt[1] * nt[2] <= 256) break;
+    }
+    const int64_t n = (int64_t)nt[0] * nt[1] * nt[2];
+    const int depth = std::min(kTileSteps, C->k - 1);
+    CoarseTiles &T = C->tiles;
+    T.n = (int)n;
+    std::vector<std::vector<int32_t>> list((size_t)n);
+    std::vector<int32_t> level, where((size_t)C->nvert, -1);
+    for (int64_t t = 0; t < n; ++t) {
+        const int64_t at[3] = {t % nt[0], (t / nt[0]) % nt[1], t / ((int64_t)nt[0] * nt[1])};
+        int lo[3], hi[3];
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = (int)(at[a] * vd[a] / nt[a]);
+            hi[a] = (int)((at[a] + 1) * vd[a] / nt[a]);
+        }
+        std::vector<int32_t> &vert = list[(size_t)t];
+        auto add = [&](int32_t v) {
+            if (where[v] >= 0) return;
+            where[v] = (int32_t)vert.size();
+            vert.push_back(v);
+        };
+        for (int z = lo[2]; z < hi[2]; ++z)
+            for (int y = lo[1]; y < hi[1]; ++y)
+                for (int x = lo[0]; x < hi[0]; ++x) add((int32_t)(x + vd[0] * (y + (int64_t)vd[1] * z)));
+        int32_t cnt[kTileSteps + 1];
+        cnt[0] = (int32_t)vert.size();
+        for (int q = 1; q <= kTileSteps; ++q) {
+            for (int32_t h = q > 1 ? cnt[q - 2] : 0; q <= depth && h < cnt[q - 1]; ++h)
+                for (int32_t e = off[vert[h]]; e < off[vert[h] + 1]; ++e) add(col[e]);
+            std::sort(vert.begin() + cnt[q - 1], vert.end());  // runs along x: neighbouring values
+            cnt[q] = (int32_t)vert.size();
+        }
+        for (const int32_t v : vert) where[v] = -1;
+        level.insert(level.end(), cnt, cnt + kTileSteps + 1);
+        T.core = std::max(T.core, cnt[0]);
+        if (depth > 0) T.rows = std::max(T.rows, cnt[depth - 1]);
+        T.verts = std::max(T.verts, cnt[depth]);
+    }
+    if (T.core > kTileCore || T.rows > kTileRows || T.verts > kTileVerts)
+        fail(SEM_EINVAL, "sem_set_coarse: a tile exceeds its bounds");
+    std::vector<int32_t> vert((size_t)n * T.verts), corner((size_t)n * T.verts * 8, -1);
+    std::vector<int16_t> lcol((size_t)n * T.rows * 32, -1);
+    for (int64_t t = 0; t < n; ++t) {
+        const std::vector<int32_t> &l = list[(size_t)t];
+        for (size_t h = 0; h < l.size(); ++h) where[l[h]] = (int32_t)h;
+        for (size_t h = 0; h < (size_t)T.verts; ++h) {
+            const int32_t v = h < l.size() ? l[h] : l[0];
+            vert[(size_t)t * T.verts + h] = v;
+            if (h >= l.size()) continue;
+            for (int32_t q = v_off[v]; q < v_off[v + 1]; ++q)
+                corner[((size_t)t * T.verts + h) * 8 + (q - v_off[v])] = v_idx[q];
+            if (depth == 0 || (int32_t)h >= level[(size_t)t * (kTileSteps + 1) + depth - 1]) continue;
+            const size_t at = (size_t)t * T.rows + h;
+            for (int32_t x = 0; x < off[v + 1] - off[v]; ++x)
+                lcol[at * 32 + (x & 7) * 4 + (x >> 3)] = (int16_t)where[col[off[v] + x]];
+        }
+        for (const int32_t v : l) where[v] = -1;
+    }
+    auto put = [&](auto &v) {
+        using X = typename std::decay_t<decltype(v)>::value_type;
+        X *p = cmalloc<X>(C, v.size());
+        if (!v.empty()) SEM_HIP(hipMemcpyAsync(p, v.data(), sizeof(X) * v.size(), hipMemcpyHostToDevice, s));
+        return p;
+    };
+    T.level = put(level);
+    T.vert = put(vert);
+    T.corner = put(corner);
+    T.col = put(lcol);
+    SEM_HIP(hipStreamSynchronize(s));  // the vectors go
+}
+
 CoarseSpace *coarse_build(sem_mesh *m, int k, double frac, hipStream_t s)
 {
     const HostMesh &h = m->h;
@@ -400,12 +578,8 @@ CoarseSpace *coarse_build(sem_mesh *m, int k, double frac, hipStream_t s)
             qw[P + i] = 0.5 * (1.0 + h.xi[i]);
         }
         C->evert = cmalloc<int32_t>(C, evert.size());
-        C->v_off = cmalloc<int32_t>(C, v_off.size());
-        C->v_idx = cmalloc<int32_t>(C, v_idx.size());
         C->qw = cmalloc<double>(C, qw.size());
         SEM_HIP(hipMemcpyAsync(C->evert, evert.data(), sizeof(int32_t) * evert.size(), hipMemcpyHostToDevice, s));
-        SEM_HIP(hipMemcpyAsync(C->v_off, v_off.data(), sizeof(int32_t) * v_off.size(), hipMemcpyHostToDevice, s));
-        SEM_HIP(hipMemcpyAsync(C->v_idx, v_idx.data(), sizeof(int32_t) * v_idx.size(), hipMemcpyHostToDevice, s));
         SEM_HIP(hipMemcpyAsync(C->qw, qw.data(), sizeof(double) * qw.size(), hipMemcpyHostToDevice, s));
         // element blocks P_e^T A_e P_e with the mesh's current operator
         std::vector<double> E8((size_t)E * 64);
@@ -490,39 +664,37 @@ CoarseSpace *coarse_build(sem_mesh *m, int k, double frac, hipStream_t s)
         C->n_coarse = 0;
         for (int64_t v = 0; v < C->nvert; ++v) C->n_coarse += diag[v] > 0.0;
         C->nnz = (int64_t)col.size();
-        C->a_off = cmalloc<int32_t>(C, off.size());
-        C->a_col = cmalloc<int32_t>(C, std::max<size_t>(col.size(), 1));
-        C->a_val = cmalloc<double>(C, std::max<size_t>(val.size(), 1));
+        std::vector<double> rows((size_t)C->nvert * 32, 0.0);
+        for (int64_t v = 0; v < C->nvert; ++v)
+            for (int32_t q = off[v]; q < off[v + 1]; ++q) {
+                const int32_t x = q - off[v];
+                rows[(size_t)v * 32 + (x & 7) * 4 + (x >> 3)] = val[q];
+            }
+        C->a_val = cmalloc<double>(C, rows.size());
         C->d0inv = cmalloc<double>(C, d0inv.size());
-        SEM_HIP(hipMemcpyAsync(C->a_off, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice, s));
-        if (!col.empty()) {
-            SEM_HIP(hipMemcpyAsync(C->a_col, col.data(), sizeof(int32_t) * col.size(), hipMemcpyHostToDevice, s));
-            SEM_HIP(hipMemcpyAsync(C->a_val, val.data(), sizeof(double) * val.size(), hipMemcpyHostToDevice, s));
-        }
+        SEM_HIP(hipMemcpyAsync(C->a_val, rows.data(), sizeof(double) * rows.size(), hipMemcpyHostToDevice, s));
         SEM_HIP(hipMemcpyAsync(C->d0inv, d0inv.data(), sizeof(double) * d0inv.size(), hipMemcpyHostToDevice, s));
         // Chebyshev coefficients
         const double theta = 0.5 * (C->b + C->a), delta = 0.5 * (C->b - C->a), sigma = theta / delta;
         C->inv_theta = 1.0 / theta;
         double rho = 1.0 / sigma;
-        C->c1.resize(k);
-        C->c2.resize(k);
+        std::vector<double> coef(2 * (size_t)k);
         for (int j = 0; j < k; ++j) {
             const double rho_new = 1.0 / (2.0 * sigma - rho);
-            C->c1[j] = rho_new * rho;
-            C->c2[j] = 2.0 * rho_new / delta;
+            coef[j] = rho_new * rho;
+            coef[k + j] = 2.0 * rho_new / delta;
             rho = rho_new;
         }
-        std::vector<double> coef(C->c1);
-        coef.insert(coef.end(), C->c2.begin(), C->c2.end());
         C->coef = cmalloc<double>(C, coef.size());
         SEM_HIP(hipMemcpyAsync(C->coef, coef.data(), sizeof(double) * coef.size(), hipMemcpyHostToDevice, s));
-        C->r0 = cmalloc<double>(C, C->nvert);
         C->z0 = cmalloc<double>(C, C->nvert);
-        C->res = cmalloc<double>(C, C->nvert);
-        C->d = cmalloc<double>(C, C->nvert);
-        C->tmp = cmalloc<double>(C, C->nvert);
+        for (int q = 0; q < 2 && coarse_launches(k) > 1; ++q) {
+            C->res[q] = cmalloc<double>(C, C->nvert);
+            C->d[q] = cmalloc<double>(C, C->nvert);
+        }
         C->partial8 = cmalloc<double>(C, (size_t)E * 8);
-        C->dot_blocks = cgrid(C->nvert * 8, kMaxCoarseDotBlocks);
+        build_tiles(C, vd, v_off, v_idx, off, col, s);
+        C->dot_blocks = std::min(C->tiles.n, kMaxCoarseDotBlocks);
         SEM_HIP(hipMemsetAsync(C->z0, 0, sizeof(double) * C->nvert, s));
         SEM_HIP(hipStreamSynchronize(s));
     } catch (...) {
@@ -568,7 +740,7 @@ static int64_t round32(int64_t n) { return (n + 31) / 32 * 32; }
 
 int64_t coarse_work_doubles(const CoarseSpace *C, int64_t E)
 {
-    return round32(E * 8) + 5 * round32(C->nvert);
+    return round32(E * 8) + (coarse_launches(C->k) > 1 ? 5 : 1) * round32(C->nvert);
 }
 
 CoarseWork coarse_work_carve(const CoarseSpace *C, int64_t E, double *base)
@@ -581,11 +753,12 @@ CoarseWork coarse_work_carve(const CoarseSpace *C, int64_t E, double *base)
         return r;
     };
     W.partial8 = take(E * 8);
-    W.r0 = take(C->nvert);
     W.z0 = take(C->nvert);
-    W.res = take(C->nvert);
-    W.d = take(C->nvert);
-    W.tmp = take(C->nvert);
+    for (int q = 0; q < 2; ++q) {
+        const bool more = coarse_launches(C->k) > 1;
+        W.res[q] = more ? take(C->nvert) : nullptr;
+        W.d[q] = more ? take(C->nvert) : nullptr;
+    }
     return W;
 }
 
@@ -604,25 +777,33 @@ void coarse_restrict(sem_mesh *m, const T *r, const T *inv, hipStream_t s)
 template void coarse_restrict<double>(sem_mesh *, const double *, const double *, hipStream_t);
 template void coarse_restrict<float>(sem_mesh *, const float *, const float *, hipStream_t);
 
+CoarseChain coarse_chain(const CoarseSpace *C, const CoarseWork &W)
+{
+    CoarseChain c;
+    c.k = C->k;
+    c.inv_theta = C->inv_theta;
+    c.coef = C->coef;
+    c.a_val = C->a_val;
+    c.d0inv = C->d0inv;
+    c.partial8 = W.partial8;
+    c.z0 = W.z0;
+    for (int q = 0; q < 2; ++q) {
+        c.res[q] = W.res[q];
+        c.d[q] = W.d[q];
+    }
+    c.tiles = C->tiles;
+    return c;
+}
+
 int coarse_solve(sem_mesh *m, double *dot_pairs, const PcgState *st, hipStream_t s)
 {
     CoarseSpace *C = m->coarse;
-    const int64_t nv = C->nvert;
-    hipLaunchKernelGGL(restrict_vert_kernel, dim3(cgrid(nv, 4096)), dim3(256), 0, s, nv, C->v_off, C->v_idx,
-                       C->partial8, C->d0inv, C->inv_theta, C->r0, C->z0, C->res, C->d, st);
-    SEM_HIP(hipGetLastError());
-    double *din = C->d, *dout = C->tmp;
-    for (int j = 0; j < C->k; ++j) {
-        if (j + 1 < C->k) {
-            hipLaunchKernelGGL(cheb_kernel<false>, dim3(C->dot_blocks), dim3(256), 0, s, nv, C->a_off, C->a_col,
-                               C->a_val, C->c1[j], C->c2[j], C->d0inv, din, dout, C->z0, C->res, C->r0, nullptr, st);
-            std::swap(din, dout);
-        } else {
-            hipLaunchKernelGGL(cheb_kernel<true>, dim3(C->dot_blocks), dim3(256), 0, s, nv, C->a_off, C->a_col,
-                               C->a_val, C->c1[j], C->c2[j], C->d0inv, din, dout, C->z0, C->res, C->r0, dot_pairs,
-                               st);
-        }
-    }
+    const CoarseChain chain =
+        coarse_chain(C, {C->partial8, C->z0, {C->res[0], C->res[1]}, {C->d[0], C->d[1]}});
+    const int launches = coarse_launches(C->k);
+    for (int q = 0; q < launches; ++q)
+        hipLaunchKernelGGL(coarse_tile_kernel, dim3(C->dot_blocks), dim3(kTileThreads), kTileLds, s, chain, q,
+                           q == launches - 1 ? dot_pairs : nullptr, st);
     SEM_HIP(hipGetLastError());
     return C->dot_blocks;
 }
@@ -713,69 +894,23 @@ __global__ __launch_bounds__(256) void batch_prolong_kernel(const SlotDesc *__re
     }
 }
 
-// vertex sums and the Chebyshev start: eight lanes per
-// vertex hold its (up to eight) element corners, added in order
+// Chebyshev launch `launch` of the slots that have one (coarse_tile)
 template <typename T>
-__global__ __launch_bounds__(256) void batch_vert_kernel(const SlotDesc *__restrict__ slots,
-                                                         const CoarseDesc *__restrict__ cd, GroupDev g, int at_start)
+__global__ __launch_bounds__(kTileThreads) void batch_tile_kernel(const SlotDesc *__restrict__ slots,
+                                                                  const CoarseDesc *__restrict__ cd, GroupDev g,
+                                                                  int launch, int at_start)
 {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
     const int64_t n = g.counts[kCountCoarse + 1];
-    const int sub = threadIdx.x & 7;
     for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
         const Item item = g.cv_items[it];
         const CoarseDesc &C = cd[item.slot];
-        if (coarse_skips<T>(slots[item.slot], at_start)) continue;
-        const int64_t v = (int64_t)item.local * kCoarseRows + (threadIdx.x >> 3);
-        const bool in = v < C.nvert;
-        const int32_t q0 = in ? C.v_off[v] : 0, q1 = in ? C.v_off[v + 1] : 0;
-        const double x = q0 + sub < q1 ? C.partial8[C.v_idx[q0 + sub]] : 0.0;
-        double s = 0.0;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const double y = __shfl(x, (threadIdx.x & 56) + c, 64);
-            if (q0 + c < q1) s += y;
-        }
-        if (in && sub == 0) {
-            C.r0[v] = s;
-            C.z0[v] = 0.0;
-            C.res[v] = s;
-            C.d[0][v] = s * C.d0inv[v] * C.inv_theta;
-        }
-    }
-}
-
-// one Chebyshev step (cheb_kernel) of the slots that have a step j
-template <typename T>
-__global__ __launch_bounds__(256) void batch_cheb_kernel(const SlotDesc *__restrict__ slots,
-                                                         const CoarseDesc *__restrict__ cd, GroupDev g, int j,
-                                                         int at_start)
-{
-    const int64_t n = g.counts[kCountCoarse + 1];
-    const int sub = threadIdx.x & 7;
-    for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
-        const Item item = g.cv_items[it];
-        const CoarseDesc &C = cd[item.slot];
-        if (j >= C.k || coarse_skips<T>(slots[item.slot], at_start)) continue;
-        const double *din = C.d[j & 1];
-        const int64_t v = (int64_t)item.local * kCoarseRows + (threadIdx.x >> 3);
-        double s = 0.0;
-        if (v < C.nvert)
-            for (int32_t q = C.a_off[v] + sub; q < C.a_off[v + 1]; q += 8) s += C.a_val[q] * din[C.a_col[q]];
-        s += __shfl_xor(s, 4, 64);
-        s += __shfl_xor(s, 2, 64);
-        s += __shfl_xor(s, 1, 64);
-        double dot = 0.0;
-        if (v < C.nvert && sub == 0) {
-            const double dv = din[v], zv = C.z0[v] + dv, rv = C.res[v] - s;
-            C.z0[v] = zv;
-            C.res[v] = rv;
-            if (j + 1 < C.k) C.d[(j + 1) & 1][v] = C.coef[j] * dv + C.coef[C.k + j] * rv * C.d0inv[v];
-            else dot = C.r0[v] * zv;
-        }
-        if (j + 1 == C.k) {
-            double p[1] = {dot};
-            __syncthreads();
+        const int launches = coarse_launches(C.chain.k);
+        if (launch >= launches || coarse_skips<T>(slots[item.slot], at_start)) continue;
+        double p[1] = {coarse_tile(C.chain, item.local, launch, reinterpret_cast<double *>(smem_raw))};
+        if (launch == launches - 1) {
             block_reduce_store<1>(p, g.cv_partial + it, 0);
+            __syncthreads();
         }
     }
 }
@@ -787,9 +922,10 @@ static hipError_t batch_coarse_t(bool at_start, int steps, const SlotDesc *slots
     const int st = at_start ? 1 : 0;
     const dim3 grid(L.vec_grid), block(256);
     hipLaunchKernelGGL(batch_restrict_kernel<T>, grid, block, 0, s, slots, cdesc, g, st);
-    hipLaunchKernelGGL(batch_vert_kernel<T>, grid, block, 0, s, slots, cdesc, g, st);
-    for (int j = 0; j < steps; ++j)
-        hipLaunchKernelGGL(batch_cheb_kernel<T>, grid, block, 0, s, slots, cdesc, g, j, st);
+    // two workgroups of a tile's size fit a compute unit
+    const dim3 tile_grid(std::min(L.vec_grid, 512));
+    for (int q = 0; q < coarse_launches(steps); ++q)
+        hipLaunchKernelGGL(batch_tile_kernel<T>, tile_grid, dim3(kTileThreads), kTileLds, s, slots, cdesc, g, q, st);
     hipLaunchKernelGGL(batch_prolong_kernel<T>, grid, block, 0, s, slots, cdesc, g, st);
     return hipGetLastError();
 }

@@ -90,24 +90,6 @@ __device__ inline void fdm_line(const double *__restrict__ M, const double (&x)[
     }
 }
 
-// Elements [lo, hi) of the workgroup's XCD (workgroups go to the 8 XCDs round
-// robin) and its place among that XCD's workgroups: each XCD walks one
-// contiguous range, so that neighbours' values are met in its own L2.
-struct XcdRange {
-    int64_t lo, hi, first, step;
-};
-__device__ inline XcdRange xcd_range(int64_t E)
-{
-    const int64_t nb = gridDim.x, groups = nb < 8 ? nb : 8;
-    const int64_t g = blockIdx.x % groups, kb = blockIdx.x / groups;
-    XcdRange x;
-    x.lo = E * g / groups;
-    x.hi = E * (g + 1) / groups;
-    x.first = x.lo + kb;
-    x.step = nb / groups + (g < nb % groups ? 1 : 0);
-    return x;
-}
-
 // One workgroup per element (persistent walk); lane (l0, l1) < n^2 owns one
 // line of the extended element in every contraction.  The element's lines are
 // gathered along t straight into registers (the x and y neighbours of a lane
