@@ -291,8 +291,10 @@ static void group_build(sem_batch *B, Group &g, const std::vector<int> &ids, hip
     SEM_HIP(hipMemcpyAsync(g.ax_count, g.h_axc.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
     SEM_HIP(hipMemcpyAsync(g.vec_first, g.h_vf.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
     SEM_HIP(hipMemcpyAsync(g.vec_count, g.h_vc.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
-    SEM_HIP(hipMemcpyAsync(g.cv_first, g.h_cvf.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
-    SEM_HIP(hipMemcpyAsync(g.cv_count, g.h_cvc.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
+    if (!g.h_cv.empty()) {  // read for slots with the coarse term only
+        SEM_HIP(hipMemcpyAsync(g.cv_first, g.h_cvf.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
+        SEM_HIP(hipMemcpyAsync(g.cv_count, g.h_cvc.data(), sizeof(int64_t) * B->max_slots, hipMemcpyHostToDevice, s));
+    }
     if (!g.h_ce.empty()) SEM_HIP(hipMemcpyAsync(g.ce_items, g.h_ce.data(), sizeof(Item) * g.h_ce.size(), hipMemcpyHostToDevice, s));
     if (!g.h_cv.empty()) SEM_HIP(hipMemcpyAsync(g.cv_items, g.h_cv.data(), sizeof(Item) * g.h_cv.size(), hipMemcpyHostToDevice, s));
     // host staging vectors must outlive the async copies
