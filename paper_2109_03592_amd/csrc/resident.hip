@@ -4,9 +4,9 @@
 // is bound by launches and by the latency of the memory chains in each
 // kernel: four launches and about 33 us an iteration for 64 elements of order
 // 7.  Here one workgroup per compute unit owns a few elements for the whole
-// run: factors in LDS, r, p, x and the Jacobi diagonal in registers, and per
-// iteration only the face values of w = A p and three scalars travel between
-// workgroups.
+// run: factors in LDS where they fit, r, p and the Jacobi diagonal in registers,
+// x in scratch memory, and per iteration only the face values of w = A p and
+// three scalars travel between workgroups.
 //
 //  * The two reductions of an iteration are also its grid barriers.  A
 //    workgroup publishes its partial sum as words that carry the iteration's
