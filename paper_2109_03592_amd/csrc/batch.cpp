@@ -116,6 +116,8 @@ struct sem_batch {
     int epw[2][SEM_MAX_ORDER + 1] = {};  // elements per operator tile, per precision and order (0: default)
     sem::BatchLaunch L{};
     hipStream_t capture = nullptr;
+    hipStream_t side[2] = {nullptr, nullptr};  // under capture: orders' operators beside each other (enqueue_ax)
+    hipEvent_t fork = nullptr, join[2] = {nullptr, nullptr};
     std::vector<void *> allocations;
     std::multimap<size_t, void *> free_bufs;
     uint64_t next_serial = 0;           // admissions so far (HostSlot::serial)
@@ -324,13 +326,47 @@ static void group_coarse(sem_batch *B, const Group &g, int prec, bool at_start, 
     if (steps > 0) SEM_HIP(batch_coarse(prec, at_start, steps, B->d_desc, B->d_cdesc, g.dev(), launch_for(B, g), s));
 }
 
+// The operators of the group's orders; in a captured FP64 iteration side by
+// side, as a few hundred elements of one order leave most of the device idle
+// (12 boxes of up to 1024 elements, us per iteration: 11 + 27 + 37 in turn, the
+// whole solve 51.3 -> 48.9 ms; boxes of up to 64 and 256 elements 13.4 -> 13.4
+// and 18.3 -> 17.3 ms).  FP32 operators are little longer than the join: mixed
+// solves of these batches took 50.9 -> 52.3, 16.8 -> 17.8 and 23.3 -> 24.4 ms
+// side by side, and stay in turn.
+static void enqueue_ax(sem_batch *B, int prec, const GroupDev &gd, const BatchLaunch &L, hipStream_t s)
+{
+    if (prec != 0 || !B->capture || s != B->capture || (L.orders & (L.orders - 1)) == 0) {
+        SEM_HIP(batch_ax(prec, 2, B->d_desc, gd, L, s));
+        return;
+    }
+    SEM_HIP(hipEventRecord(B->fork, s));
+    int q = 0;
+    for (int N = SEM_MAX_ORDER; N >= 1; --N) {
+        if (!(L.orders & (1u << N))) continue;
+        BatchLaunch one = L;
+        one.orders = 1u << N;
+        const int lane = q++ % 3;  // two streams beside the group's own
+        if (lane == 0) {
+            SEM_HIP(batch_ax(prec, 2, B->d_desc, gd, one, s));
+            continue;
+        }
+        hipStream_t side = B->side[lane - 1];
+        SEM_HIP(hipStreamWaitEvent(side, B->fork, 0));
+        SEM_HIP(batch_ax(prec, 2, B->d_desc, gd, one, side));
+    }
+    for (int i = 0; i < 2 && i + 1 < q; ++i) {
+        SEM_HIP(hipEventRecord(B->join[i], B->side[i]));
+        SEM_HIP(hipStreamWaitEvent(s, B->join[i], 0));
+    }
+}
+
 // one CG iteration of every slot in g, precision prec
 static void enqueue_batch_iters(sem_batch *B, Group &g, int prec, int k, unsigned orders, int steps, hipStream_t s)
 {
     const GroupDev gd = g.dev();
     const BatchLaunch L = launch_for(B, orders, g.prec);
     for (int it = 0; it < k; ++it) {
-        SEM_HIP(batch_ax(prec, 2, B->d_desc, gd, L, s));
+        enqueue_ax(B, prec, gd, L, s);
         SEM_HIP(batch_gs(prec, 1, B->d_desc, gd, L, s));
         SEM_HIP(batch_reduce_sigma(prec, B->d_desc, gd, L, s));
         SEM_HIP(batch_update(prec, B->d_desc, gd, L, s));
@@ -356,7 +392,10 @@ static void run_batch_iters(sem_batch *B, Group &g, int prec, int k, bool use_gr
             SEM_HIP(hipGraphExecDestroy(g.graph));
             g.graph = nullptr;
         }
-        if (!B->capture) SEM_HIP(hipStreamCreateWithFlags(&B->capture, hipStreamNonBlocking));
+        for (hipStream_t *q : {&B->capture, &B->side[0], &B->side[1]})
+            if (!*q) SEM_HIP(hipStreamCreateWithFlags(q, hipStreamNonBlocking));
+        for (hipEvent_t *e : {&B->fork, &B->join[0], &B->join[1]})
+            if (!*e) SEM_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
         hipGraph_t gr = nullptr;
         SEM_HIP(hipStreamBeginCapture(B->capture, hipStreamCaptureModeThreadLocal));
         try {
@@ -818,6 +857,10 @@ sem_status sem_batch_free(sem_batch *B)
     for (Group *g : {&B->g64, &B->g32, &B->gres})
         if (g->graph) hipGraphExecDestroy(g->graph);
     if (B->capture) hipStreamDestroy(B->capture);
+    for (hipStream_t q : B->side)
+        if (q) hipStreamDestroy(q);
+    for (hipEvent_t e : {B->fork, B->join[0], B->join[1]})
+        if (e) hipEventDestroy(e);
     for (void *p : B->allocations) hipFree(p);
     delete B;
     return SEM_OK;
