@@ -573,6 +573,7 @@ static void enqueue_iterations(sem_mesh *m, int k, hipStream_t s, Profiler *prof
     for (int it = 0; it < k; ++it) {
         if (prof) prof->mark(s);
         int64_t axb = 0;
+        bool gs_sigma = false;
         if (fused) {
             axb = enqueue_axgs_fused<T>(m, *fused, 2, Prec<T>::r(m), Prec<T>::w(m), s);
             if (prof) prof->mark(s);
@@ -580,10 +581,14 @@ static void enqueue_iterations(sem_mesh *m, int k, hipStream_t s, Profiler *prof
         } else {
             axb = enqueue_ax<T>(m, mode, schwarz ? zs : Prec<T>::r(m), Prec<T>::w(m), s);
             if (prof) prof->mark(s);
-            if (!update_gs) enqueue_gs<T>(m, Prec<T>::w(m), st, s);
+            // (a profiled iteration keeps the phases apart)
+            gs_sigma = !prof && !update_gs && m->gs_lattice_ok && m->gs_kind != SEM_GS_PLAN &&
+                       !gs_streams(m->gsl, m->gs_kind == SEM_GS_STREAM);
+            if (gs_sigma) SEM_HIP(launch_gs_lattice_sigma<T>(m->gsl, Prec<T>::w(m), m->partials, axb, st, s));
+            else if (!update_gs) enqueue_gs<T>(m, Prec<T>::w(m), st, s);
         }
         if (prof) prof->mark(s);
-        SEM_HIP(launch_reduce_sigma(m->partials, axb, st, s));
+        if (!gs_sigma) SEM_HIP(launch_reduce_sigma(m->partials, axb, st, s));
         int64_t pairs = ub;
         if (coarse) {
             // restriction fused into the update; <r, P z0> = <P^T r, z0>: the

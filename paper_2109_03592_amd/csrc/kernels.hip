@@ -419,43 +419,47 @@ __global__ __launch_bounds__(256) void pcg_update_gs_kernel(GsLattice L, int64_t
 }
 
 // ---------------------------------------------------------------------------
-// single-workgroup reductions of partials (fixed order)
-template <int NV>
+// single-workgroup reductions of partials: a fixed order, that of 1024 threads
+// (a smaller workgroup stands in for V threads with each of its own)
+template <int NV, int V = 1>
 __device__ inline void sum_partials(const double *__restrict__ partial, int64_t n, double (&out)[NV])
 {
     __shared__ double red[NV][1024];
-    // eight partial sums per thread (eight loads in flight), combined in order
-    constexpr int K = 8;
-    double s[NV], acc[K][NV];
-#pragma unroll
-    for (int c = 0; c < K; ++c)
-#pragma unroll
-        for (int q = 0; q < NV; ++q) acc[c][q] = 0.0;
-    const int64_t B = blockDim.x;
-    int64_t b = threadIdx.x;
-    for (; b + (K - 1) * B < n; b += K * B)
+    const int64_t B = (int64_t)blockDim.x * V;
+#pragma unroll 1
+    for (int v = 0; v < V; ++v) {
+        // eight partial sums per thread (eight loads in flight), combined in order
+        constexpr int K = 8;
+        double s[NV], acc[K][NV];
 #pragma unroll
         for (int c = 0; c < K; ++c)
 #pragma unroll
-            for (int q = 0; q < NV; ++q) acc[c][q] += partial[(b + c * B) * NV + q];
+            for (int q = 0; q < NV; ++q) acc[c][q] = 0.0;
+        const int t = threadIdx.x + v * blockDim.x;
+        int64_t b = t;
+        for (; b + (K - 1) * B < n; b += K * B)
 #pragma unroll
-    for (int c = 0; c < K; ++c)
-        if (b + c * B < n)
+            for (int c = 0; c < K; ++c)
 #pragma unroll
-            for (int q = 0; q < NV; ++q) acc[c][q] += partial[(b + c * B) * NV + q];
+                for (int q = 0; q < NV; ++q) acc[c][q] += partial[(b + c * B) * NV + q];
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        s[q] = 0.0;
+        for (int c = 0; c < K; ++c)
+            if (b + c * B < n)
 #pragma unroll
-        for (int c = 0; c < K; ++c) s[q] += acc[c][q];
+                for (int q = 0; q < NV; ++q) acc[c][q] += partial[(b + c * B) * NV + q];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            s[q] = 0.0;
+#pragma unroll
+            for (int c = 0; c < K; ++c) s[q] += acc[c][q];
+            red[q][t] = s[q];
+        }
     }
-#pragma unroll
-    for (int q = 0; q < NV; ++q) red[q][threadIdx.x] = s[q];
     __syncthreads();
-    for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
+    for (int h = (int)(B / 2); h > 0; h >>= 1) {
+        for (int t = threadIdx.x; t < h; t += blockDim.x)
 #pragma unroll
-            for (int q = 0; q < NV; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + h];
+            for (int q = 0; q < NV; ++q) red[q][t] += red[q][t + h];
         __syncthreads();
     }
 #pragma unroll
@@ -471,17 +475,45 @@ __global__ __launch_bounds__(1024) void reduce_scalar_kernel(const double *__res
 }
 
 // sigma = <p, A p>; alpha = rho / sigma (breakdown when sigma <= 0 or not finite)
+// alpha = rho / sigma, or a breakdown
+__device__ inline void set_alpha(PcgState *st, double sigma)
+{
+    st->sigma = sigma;
+    if (!(sigma > 0.0) || !isfinite(sigma)) st->done = 2;
+    else st->alpha = st->rho / sigma;
+}
+
 __global__ __launch_bounds__(1024) void reduce_sigma_kernel(const double *__restrict__ partial, int64_t n,
                                                             PcgState *__restrict__ st)
 {
     if (st->done) return;
     double s[1];
     sum_partials<1>(partial, n, s);
-    if (threadIdx.x == 0) {
-        st->sigma = s[0];
-        if (!(s[0] > 0.0) || !isfinite(s[0])) st->done = 2;
-        else st->alpha = st->rho / s[0];
+    if (threadIdx.x == 0) set_alpha(st, s[0]);
+}
+
+// gs_lattice_kernel and reduce_sigma_kernel in one launch: neither needs the
+// other's result, and the sum's 4.5 us are gone beside a gather-scatter of 5 to
+// 11 us (CG with the coarse term, 16x16x16 elements of N = 7: 99.8 -> 97.9 us per
+// iteration, 11x7x9 of N = 5: 39.4 -> 36.9).  The first workgroup sums, in the order of reduce_sigma_kernel.
+// (Where it finds a breakdown, w may be left half assembled: nothing reads it.)
+template <typename T>
+__global__ __launch_bounds__(256) void gs_lattice_sigma_kernel(GsLattice L, T *__restrict__ v,
+                                                               const double *__restrict__ partial, int64_t n,
+                                                               PcgState *__restrict__ st)
+{
+    if (st->done) return;
+    if (blockIdx.x == 0) {
+        double s[1];
+        sum_partials<1, 4>(partial, n, s);
+        if (threadIdx.x == 0) set_alpha(st, s[0]);
+        return;
     }
+    const unsigned nb = gridDim.x - 1, b = blockIdx.x - 1;
+    const unsigned per = nb / 8, rem = nb % 8, xcd = b % 8, kb = b / 8;
+    const unsigned lb = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + kb;
+    const int64_t t = (int64_t)lb * blockDim.x + threadIdx.x;
+    if (t < L.n_nodes) gs_lattice_node<T>(L, t, v);
 }
 
 // rho' = <r, z>, rr = <r, r>; beta = rho'/rho; convergence / limit flags
@@ -866,15 +898,37 @@ __global__ __launch_bounds__(256) void gs_stream_kernel(GsLattice L, GsLattice L
     if (t < Lz.n_nodes) gs_lattice_node<T>(Lz, t, v);
 }
 
+static int64_t gs_row_walks(const GsLattice &L)
+{
+    return (int64_t)(L.periodic[1] ? L.nel[1] : L.nel[1] + 1) * (L.N - 1) * L.nel[2];
+}
+
+// measured: the row walks win at N = 7 once there are enough of them to fill
+// the device; at lower orders most lanes of a wave are idle and on small meshes
+// the walks are too few, and the per-node kernel is faster
+bool gs_streams(const GsLattice &L, bool force_stream)
+{
+    return L.N >= 2 && L.N <= 7 && (force_stream || (L.N == 7 && gs_row_walks(L) >= 2048));
+}
+
+template <typename T>
+hipError_t launch_gs_lattice_sigma(const GsLattice &L, T *v, const double *partial, int64_t n, PcgState *st,
+                                   hipStream_t s)
+{
+    const int64_t blocks = (L.n_nodes + 255) / 256 + 1;
+    hipLaunchKernelGGL((gs_lattice_sigma_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, s, L, v, partial, n, st);
+    return hipGetLastError();
+}
+template hipError_t launch_gs_lattice_sigma<double>(const GsLattice &, double *, const double *, int64_t, PcgState *,
+                                                    hipStream_t);
+template hipError_t launch_gs_lattice_sigma<float>(const GsLattice &, float *, const double *, int64_t, PcgState *,
+                                                   hipStream_t);
+
 template <typename T>
 hipError_t launch_gs_lattice(const GsLattice &L, T *v, const PcgState *st, hipStream_t s, bool force_stream)
 {
-    const int64_t ngy = L.periodic[1] ? L.nel[1] : L.nel[1] + 1;
-    const int64_t nwaves = ngy * (L.N - 1) * L.nel[2];
-    // measured: the row walks win at N = 7 once there are enough of them to
-    // fill the device; at lower orders most lanes of a wave are idle and on
-    // small meshes the walks are too few, and the per-node kernel is faster
-    const bool stream = L.N >= 2 && L.N <= 7 && (force_stream || (L.N == 7 && nwaves >= 2048));
+    const int64_t nwaves = gs_row_walks(L);
+    const bool stream = gs_streams(L, force_stream);
     if (stream) {
         GsLattice Lz{};
         if (!gs_lattice_make(L.N, L.nel, L.periodic, L.faces, Lz, true)) return hipErrorInvalidValue;

@@ -61,6 +61,12 @@ template <typename T>
 // force_stream: the row-streaming kernel at every order 2..7 (by default only
 // at N = 7 with at least 2048 row walks, where it is the faster one)
 hipError_t launch_gs_lattice(const GsLattice &L, T *v, const PcgState *st, hipStream_t s, bool force_stream = false);
+// whether launch_gs_lattice takes the row-streaming kernel
+bool gs_streams(const GsLattice &L, bool force_stream);
+// the per-node kernel and launch_reduce_sigma in one launch
+template <typename T>
+hipError_t launch_gs_lattice_sigma(const GsLattice &L, T *v, const double *partial, int64_t n, PcgState *st,
+                                   hipStream_t s);
 
 template <typename T>
 hipError_t launch_gs(const GsPlan &plan, const int32_t *off, const int32_t *idx, T *v, bool zero_only,
