@@ -70,6 +70,23 @@ static T *dalloc(sem_mesh *m, size_t count)
     return static_cast<T *>(p);
 }
 
+// memory a call can do without: null when the device has none left
+template <typename T>
+static T *dalloc_if_room(sem_mesh *m, size_t count)
+{
+    void *p = nullptr;
+    const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
+    const hipError_t e = hipMalloc(&p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();  // it is dealt with here
+        return nullptr;
+    }
+    SEM_HIP(e);
+    m->allocations.push_back(p);
+    m->device_bytes += bytes;
+    return static_cast<T *>(p);
+}
+
 static void upload(void *dst, const void *src, size_t bytes, hipStream_t s)
 {
     SEM_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s));
@@ -799,17 +816,26 @@ static bool resident_for(const sem_mesh *m, ResidentShape &sh, int &cus)
     return resident_shape(m->h.N, m->h.E, sizeof(T), cus, (size_t)lds, sh);
 }
 
+// Memory of the mesh's resident runs; false when the device has none left (the
+// general iteration does without).
+static bool resident_space(sem_mesh *m)
+{
+    if (!m->res_x) m->res_x = dalloc_if_room<double>(m, m->h.nL);
+    if (m->res_x && !m->res_words) {
+        m->res_words = dalloc_if_room<uint64_t>(m, kResidentWords);
+        m->res_seq = 0;
+    }
+    return m->res_x && m->res_words;
+}
+
 // Up to k iterations resident on the chip; false when the workgroups did not
-// meet: nothing has changed then.  hs receives the state afterwards.
+// meet or there is no memory for the run: nothing has changed then.  hs
+// receives the state afterwards.
 template <typename T>
 static bool run_resident(sem_mesh *m, const ResidentShape &sh, int cus, int k, PcgState &hs, hipStream_t s)
 {
+    if (!resident_space(m)) return false;
     ResidentSeat seat(m->device, sh.nwg, cus);
-    if (!m->res_words) {
-        m->res_words = dalloc<uint64_t>(m, kResidentWords);
-        m->res_x = dalloc<double>(m, m->h.nL);
-        m->res_seq = 0;
-    }
     if (m->res_seq == 0 || m->res_seq > UINT32_MAX - 2 * kResidentIters) {
         SEM_HIP(hipMemsetAsync(m->res_words, 0, sizeof(uint64_t) * kResidentWords, s));
         m->res_seq = 0;

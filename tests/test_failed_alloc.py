@@ -1,0 +1,41 @@
+"""Solves on a device that runs out of memory (CPU: fake_hip.cpp): whichever
+allocation of a solve fails, that call and every later one work on memory that
+is there."""
+import pytest
+
+import fakehip
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    return fakehip.build(tmp_path_factory.mktemp("fakehip"))
+
+
+# the mesh of 8 elements takes the resident run: its scratch is not needed by
+# the general iteration, which a mesh without room for it goes on with
+def test_resident_scratch(runtime):
+    out = fakehip.run(runtime, """
+        # the solve vectors first (profiled solves keep to the general iteration)
+        for nth in range(3):
+            m, info = mesh(4, (2, 2, 2), fp32=True)
+            b, x = np.ones(info.n_local), np.zeros(info.n_local)
+            o = opts(fixed_iters=4, use_graph=0, profile=1)
+            L.check(lib.sem_pcg_solve(m, b.ctypes.data, x.ctypes.data, C.byref(o), None, None), "solve")
+            assert not launches("resident_kernel")
+            o = opts(fixed_iters=4, use_graph=0)
+            fake.fake_fail_in(nth)
+            st = lib.sem_pcg_solve(m, b.ctypes.data, x.ctypes.data, C.byref(o), None, None)
+            fake.fake_fail_in(-1)
+            assert st == L.SEM_OK, (nth, st)
+            fake.fake_clear()
+            for _ in range(2):
+                st = lib.sem_pcg_solve(m, b.ctypes.data, x.ctypes.data, C.byref(o), None, None)
+                assert st == L.SEM_OK, (nth, st)
+            runs = launches("resident_kernel")
+            assert len(runs) == 2 and all(fake.fake_has_scratch(i) for i in runs), (nth, runs)
+            fake.fake_clear()
+            lib.sem_free(m)
+        assert fake.fake_null_uses() == 0
+        print("done")
+        """)
+    assert "done" in out
