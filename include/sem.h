@@ -154,7 +154,7 @@ sem_status sem_load_geometry(sem_mesh *mesh, const double *G, const double *B, v
  * level (their partial sums follow the workgroups).  Setting it applies to
  * every operator launch of the mesh; by default each precision and use (plain,
  * Helmholtz, CG, CG with the coarse term) has its own count, measured per
- * order, with one element per workgroup on small meshes from order 8 on.
+ * order and number of elements.
  * sem_get_operator_config reads the FP64 CG one. */
 sem_status sem_set_operator_config(sem_mesh *mesh, int epw, int grid);
 sem_status sem_get_operator_config(const sem_mesh *mesh, int *epw, int *grid);

@@ -157,16 +157,59 @@ static OperatorEpw default_epw(int N, int64_t E)
     // FP32 plain: N=2 262k 99: 90; N=4 125k 163: 135; N=6 33k 83: 78
     o.cg32 = cg32[N - 2];
     o.plain32 = plain32[N - 2];
+    // Orders 2 to 7: the larger tile of a pair wins where its workgroups still
+    // give every compute unit several of them, the smaller one below (the table
+    // was taken from the large ones; us per launch, table's count: the other).
+    // N=2 plain: 19683 elements 12.7: 11.1, 47952 28.8: 28.0, 50653 29.3: 31.2;
+    // FP32 64000 23.4: 23.2, 79507 28.8: 29.5; Helmholtz 19683 15.4: 13.0, from
+    // 50653 on level
+    if (N == 2) {
+        if (E < 49152) o.plain = 7;
+        if (E < 71680) o.plain32 = 7;
+        o.helm = 7;
+    }
+    // N=3 plain: 2197 5.8: 5.5, 35937 26.6: 25.5, 42875 30.5: 29.9, 46656 32.9:
+    // 33.4; Helmholtz 15625 16.1: 15.3, 25230 24.6: 22.9, 29791 26.9: 28.4
+    if (N == 3) {
+        if (E < 45056) o.plain = 4;
+        if (E < 27648) o.helm = 4;
+    }
+    // N=4 CG: 2197 31.2: 29.5, 8000 61.4: 60.7, 11132 74.0: 76.0; 15360 elements
+    // are four workgroups for each compute unit, and what is beyond them runs
+    // alone: 15625 100.9: 99.5, 19683 122.4: 119.9, 21952 129.1: 129.9
+    if (N == 4 && (E <= 8192 || (E > 15360 && E <= 20480))) o.cg = 5;
+    // N=6: one element each past the 4096 workgroups of the grid, where nine
+    // (five in FP32) still fill two (four) workgroups for each compute unit: CG
+    // 4352 98.1: 89.5, 4608 98.7: 90.7, 4913 101.5: 108.1; with the coarse term
+    // 4608 97.3: 93.4, 4913 99.9: 106.7; FP32 plain 5120 17.0: 14.8, 5202 17.2: 19.2
+    if (N == 6 && E > 4096 && E <= 4608) o.cg = o.column = 9;
+    if (N == 6 && E > 4096 && E <= 5120) o.plain32 = 5;
+    // N=7 CG: 27 elements 31.1: 28.7, 36 36.7: 38.7; with the coarse term 64
+    // 32.9: 31.8, 343 39.0: 38.5, 512 40.7: 41.5
+    if (N == 7 && E <= 32) o.cg = 4;
+    if (N == 7 && E <= 384) o.column = 4;
     // N=9 fills five of a workgroup's 512 lanes best, but then a compute unit
     // holds one workgroup and every barrier stops all of it; the fuller waves
     // win on large meshes only.  FP64, 4096 elements 71: 57, 50653 694: 690,
-    // 110592 1501 against 1524; FP32 8000 61: 54, 13824 96 against 100
-    if (N == 9 && E < 65536) o.plain = o.helm = 1;
+    // 110592 1501 against 1524; Helmholtz 27000 454: 444, 35937 590 against 594;
+    // FP32 8000 61: 54, 13824 96 against 100
+    if (N == 9 && E < 65536) o.plain = 1;
+    if (N == 9 && E < 32768) o.helm = 1;
     if (N == 9 && E < 10240) o.plain32 = 1;
     // up to four elements per compute unit the work of one workgroup counts,
     // not the waves: N=9 512 elements 18: 14, N=12 512 38: 30 (FP32 21: 18);
-    // CG N=12 1000 182: 150
-    if (N >= 8 && E <= 1024) o.cg = o.plain = o.helm = o.plain32 = 1;
+    // CG N=12 1000 182: 150.  At three of them, one workgroup of three each:
+    // 729 elements N=8 plain 14.0: 12.9, Helmholtz 14.1: 13.2, FP32 9.8: 9.6;
+    // N=11 plain 28.3: 25.5, Helmholtz 35.4: 25.7; N=12 plain 37.9: 36.9
+    // (Helmholtz 39.4 against 40.2); N=8 plain 343 elements 12.8: 12.4
+    if (N >= 8 && E <= 1024) {
+        o.cg = o.plain = o.helm = o.plain32 = 1;
+        const bool three = E > 512 && E <= 768;
+        if (three && (N == 8 || N == 11)) o.plain = o.helm = 3;
+        if (three && N == 8) o.plain32 = 3;
+        if (three && N == 12) o.plain = 3;
+        if (N == 8 && E > 256 && E <= 512) o.plain = 3;
+    }
     return o;
 }
 
