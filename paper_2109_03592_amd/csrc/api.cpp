@@ -35,6 +35,8 @@ void fail(sem_status st, const std::string &msg)
 void check_hip(hipError_t e, const char *what)
 {
     if (e != hipSuccess) {
+        // the error is this call's: left in the runtime, the next launch's check would find it
+        (void)hipGetLastError();
         const sem_status st = (e == hipErrorOutOfMemory) ? SEM_ENOMEM : SEM_EHIP;
         fail(st, std::string(what) + ": " + hipGetErrorString(e));
     }

@@ -39,3 +39,14 @@ def test_resident_scratch(runtime):
         print("done")
         """)
     assert "done" in out
+
+
+def test_error_ends_with_its_call(runtime):
+    """A call that ran out of memory leaves no error behind for the next."""
+    fakehip.run(runtime, """
+        m, info = mesh(3, (2, 2, 2))
+        u, w = np.ones(info.n_local), np.zeros(info.n_local)
+        fake.fake_fail_in(0)
+        assert lib.sem_set_helmholtz(m, u.ctypes.data, u.ctypes.data, None) == L.SEM_ENOMEM
+        assert lib.sem_ax(m, 0, u.ctypes.data, w.ctypes.data, None, None) == L.SEM_OK
+        """)
