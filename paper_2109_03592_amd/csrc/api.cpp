@@ -522,10 +522,12 @@ static void axgs_build_shape(sem_mesh *m)
         sh.res_copies = (int64_t)idx.size();
         SEM_HIP(hipMalloc((void **)&sh.res_off, sizeof(int32_t) * off.size()));
         sh.owns_plan = true;
-        if (hipMalloc((void **)&sh.res_idx, sizeof(int32_t) * std::max<size_t>(idx.size(), 1)) != hipSuccess) {
+        try {
+            SEM_HIP(hipMalloc((void **)&sh.res_idx, sizeof(int32_t) * std::max<size_t>(idx.size(), 1)));
+        } catch (...) {
             hipFree(sh.res_off);
             sh = AxgsShape();
-            fail(SEM_ENOMEM, "fused operator: residual plan");
+            throw;
         }
         hipStream_t s = nullptr;
         SEM_HIP(hipMemcpyAsync(sh.res_off, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice, s));

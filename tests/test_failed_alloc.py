@@ -42,11 +42,32 @@ def test_resident_scratch(runtime):
 
 
 def test_error_ends_with_its_call(runtime):
-    """A call that ran out of memory leaves no error behind for the next."""
+    """A call that ran out of memory, at whichever of its allocations, leaves
+    no error behind for the next."""
     fakehip.run(runtime, """
         m, info = mesh(3, (2, 2, 2))
         u, w = np.ones(info.n_local), np.zeros(info.n_local)
-        fake.fake_fail_in(0)
-        assert lib.sem_set_helmholtz(m, u.ctypes.data, u.ctypes.data, None) == L.SEM_ENOMEM
-        assert lib.sem_ax(m, 0, u.ctypes.data, w.ctypes.data, None, None) == L.SEM_OK
+        def axgs():
+            st = lib.sem_set_axgs_config(m, 1, 0, 0)
+            return st or lib.sem_axgs(m, 0, u.ctypes.data, w.ctypes.data, None)
+        def proj():
+            p = C.c_void_p()
+            st = lib.sem_proj_create(m, 2, C.byref(p))
+            lib.sem_proj_free(p)
+            return st
+        calls = [axgs, proj, lambda: lib.sem_set_helmholtz(m, u.ctypes.data, u.ctypes.data, None),
+                 lambda: lib.sem_set_schwarz(m, 1, None)]
+        for c, call in enumerate(calls):
+            refused = 0
+            for nth in range(100):
+                fake.fake_fail_in(nth)
+                st = call()
+                fake.fake_fail_in(-1)
+                lib.sem_set_axgs_config(m, 0, 0, 0)
+                assert lib.sem_ax(m, 0, u.ctypes.data, w.ctypes.data, None, None) == L.SEM_OK, (c, nth)
+                if st == L.SEM_OK:
+                    break
+                assert st == L.SEM_ENOMEM, (c, nth, st)
+                refused += 1
+            assert refused > 0, c
         """)
