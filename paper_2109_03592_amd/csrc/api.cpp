@@ -72,6 +72,14 @@ static T *dalloc(sem_mesh *m, size_t count)
     return static_cast<T *>(p);
 }
 
+// a vector of the mesh that is allocated when first needed: each is its own
+// test, so a call that was refused one leaves the rest for the next
+template <typename T>
+static void ensure(sem_mesh *m, T *&p, size_t count)
+{
+    if (!p) p = dalloc<T>(m, count);
+}
+
 // memory a call can do without: null when the device has none left
 template <typename T>
 static T *dalloc_if_room(sem_mesh *m, size_t count)
@@ -281,18 +289,9 @@ static void require_device_gfx950()
 static void ensure_solve_space(sem_mesh *m, bool need32)
 {
     const int64_t nL = m->h.nL;
-    if (!m->r64) {
-        m->r64 = dalloc<double>(m, nL);
-        m->p64 = dalloc<double>(m, nL);
-        m->w64 = dalloc<double>(m, nL);
-        m->x64 = dalloc<double>(m, nL);
-    }
-    if (need32 && !m->r32) {
-        m->x32 = dalloc<float>(m, nL);
-        m->r32 = dalloc<float>(m, nL);
-        m->p32 = dalloc<float>(m, nL);
-        m->w32 = dalloc<float>(m, nL);
-    }
+    for (double **v : {&m->r64, &m->p64, &m->w64, &m->x64}) ensure(m, *v, nL);
+    if (need32)
+        for (float **v : {&m->x32, &m->r32, &m->p32, &m->w32}) ensure(m, *v, nL);
 }
 
 static hipStream_t cap_stream(sem_mesh *m)
@@ -1466,13 +1465,10 @@ sem_status sem_set_helmholtz(sem_mesh *m, const double *h1, const double *h2, vo
         const int64_t nL = m->h.nL;
         drop_graphs(m, s);
         const bool helm = h1 || h2;
-        if (helm && !m->h1_64) {
-            m->h1_64 = dalloc<double>(m, nL);
-            m->h2b64 = dalloc<double>(m, nL);
-            if (m->with_fp32) {
-                m->h1_32 = dalloc<float>(m, nL);
-                m->h2b32 = dalloc<float>(m, nL);
-            }
+        if (helm) {
+            for (double **v : {&m->h1_64, &m->h2b64}) ensure(m, *v, nL);
+            if (m->with_fp32)
+                for (float **v : {&m->h1_32, &m->h2b32}) ensure(m, *v, nL);
         }
         if (helm) {
             if (h1) SEM_HIP(hipMemcpyAsync(m->h1_64, h1, sizeof(double) * nL, hipMemcpyDeviceToDevice, s));

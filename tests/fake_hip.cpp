@@ -25,7 +25,7 @@ std::set<void *> blocks;
 std::vector<Launch> launches;
 hipError_t last = hipSuccess;  // kept until it is read, as the runtime does
 int fail_in = -1;              // allocations until one fails
-int null_uses = 0;             // copies and fills of no memory
+int null_uses = 0;             // copies, fills and kernels given no memory
 int verdict = 0;               // what a resident run leaves in its state
 int64_t allocated = 0, copied = 0;
 
@@ -99,6 +99,16 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t ld
     if (l.name.find("resident_kernel") != std::string::npos) {
         if (l.name.find("resident_kernelId") != std::string::npos) resident<double>(l, args);
         else resident<float>(l, args);
+    }
+    // kernels of a few pointers: (n, value, out), (n, a, b, out), (n, state, x, p)
+    auto given = [&](int k) {
+        if (!*static_cast<void **>(args[k])) null_uses++;
+    };
+    if (l.name.find("fill_kernel") != std::string::npos) given(2);
+    if (l.name.find("scale_kernel") != std::string::npos || l.name.find("pcg_finish_kernel") != std::string::npos) {
+        given(1);
+        given(2);
+        given(3);
     }
     launches.push_back(l);
     return hipSuccess;

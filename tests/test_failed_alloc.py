@@ -71,3 +71,27 @@ def test_error_ends_with_its_call(runtime):
                 refused += 1
             assert refused > 0, c
         """)
+
+
+def test_work_vectors(runtime):
+    """Whichever work vector of a first solve, or coefficient of a first
+    Helmholtz form, is refused: the next call has all of them."""
+    fakehip.run(runtime, """
+        def call(m, info, kind):
+            b, x = np.ones(info.n_local), np.zeros(info.n_local)
+            if kind == "helmholtz":
+                return lib.sem_set_helmholtz(m, b.ctypes.data, b.ctypes.data, None)
+            o = opts(fixed_iters=2, use_graph=0, profile=1)
+            if kind == "mixed":
+                o = opts(precision=L.SEM_PREC_MIXED, profile=1)
+            return lib.sem_pcg_solve(m, b.ctypes.data, x.ctypes.data, C.byref(o), None, None)
+        for kind, refusals in (("fp64", 4), ("mixed", 8), ("helmholtz", 5)):
+            for nth in range(refusals):
+                m, info = mesh(3, (2, 2, 2), fp32=True)
+                fake.fake_fail_in(nth)
+                assert call(m, info, kind) == L.SEM_ENOMEM, (kind, nth)
+                fake.fake_fail_in(-1)
+                assert call(m, info, kind) == L.SEM_OK, (kind, nth)
+                assert fake.fake_null_uses() == 0, (kind, nth)
+                lib.sem_free(m)
+        """)
