@@ -184,6 +184,18 @@ enum { SEM_GS_AUTO = 0, SEM_GS_PLAN = 1, SEM_GS_STREAM = 2 };
 sem_status sem_set_gs_config(sem_mesh *mesh, int kind);
 sem_status sem_get_gs_config(const sem_mesh *mesh, int *kind, int *lattice_in_use);
 
+/* The resident CG of a small mesh (sem_pcg_solve): enable = 0 keeps the mesh's
+ * solves to the general iteration, 1 (the default) takes a resident run
+ * wherever one applies.  wait_ms: how long the workgroups of a run wait for
+ * each other before it is called off, at most 1000; negative: the default of
+ * 20; 0: no run stands, whether its workgroups met or not, so that every solve goes
+ * through the hand-over to the general iteration.
+ * sem_get_resident_info: whether the mesh's FP64 solves take resident runs as
+ * things are (operator, preconditioner, enable), and how many of its runs have
+ * stood and have been called off.
+ * Errors: SEM_EINVAL (null mesh, enable not 0 or 1, wait_ms beyond 1000). */
+sem_status sem_set_resident_config(sem_mesh *mesh, int enable, double wait_ms);
+sem_status sem_get_resident_info(const sem_mesh *mesh, int *in_use, int64_t *runs, int64_t *called_off);
 
 /* Fused operator and gather-scatter (Algorithm 1 followed by section 2's
  * exchange of element face values, done in one launch for the faces a

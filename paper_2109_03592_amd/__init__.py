@@ -168,6 +168,21 @@ class Mesh:
         L.check(self._lib.sem_get_gs_config(self._h, C.byref(k), C.byref(on)), "sem_get_gs_config")
         return ("auto", "plan", "stream")[k.value], bool(on.value)
 
+    def set_resident(self, enable: bool = True, wait_ms: float = -1.0):
+        """The resident CG of small meshes on or off, and how long a run's
+        workgroups wait for each other (negative: the default of 20 ms; 0: no
+        run stands, every solve is handed over to the general iteration)."""
+        L.check(self._lib.sem_set_resident_config(self._h, int(bool(enable)), float(wait_ms)),
+                "sem_set_resident_config")
+
+    def resident_info(self) -> dict:
+        """Whether FP64 solves take resident runs, and the runs that stood and
+        were called off so far."""
+        on, runs, off = C.c_int(), C.c_int64(), C.c_int64()
+        L.check(self._lib.sem_get_resident_info(self._h, C.byref(on), C.byref(runs), C.byref(off)),
+                "sem_get_resident_info")
+        return {"in_use": bool(on.value), "runs": int(runs.value), "called_off": int(off.value)}
+
     def set_axgs_config(self, enable: bool = True, epw: int = 0, lines_per_wg: int = 0):
         """Fused operator and gather-scatter: on/off, elements per tile and
         x-lines per workgroup (0 = automatic)."""

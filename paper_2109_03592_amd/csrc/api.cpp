@@ -851,7 +851,7 @@ constexpr uint64_t kResidentWait = 2000000;
 template <typename T>
 static bool resident_for(const sem_mesh *m, ResidentShape &sh, int &cus)
 {
-    if (coarse_cg<T>(m) || schwarz_cg<T>(m) || m->helm || !m->gs_lattice_ok || (m->axgs && m->axgs->enabled) ||
+    if (!m->res_enable || coarse_cg<T>(m) || schwarz_cg<T>(m) || m->helm || !m->gs_lattice_ok || (m->axgs && m->axgs->enabled) ||
         m->h.nL >= INT32_MAX)
         return false;
     int lds = 0;
@@ -903,12 +903,17 @@ static bool run_resident(sem_mesh *m, const ResidentShape &sh, int cus, int k, P
     a.words = m->res_words;
     a.seq = m->res_seq;
     a.iters = std::min(k, kResidentIters);
-    a.wait_ticks = kResidentWait;
+    a.wait_ticks = m->res_wait_ms < 0.0 ? kResidentWait : (uint64_t)(m->res_wait_ms * 1e5);
     m->res_seq += (uint32_t)a.iters;
-    SEM_HIP(hipMemsetAsync(&a.st->pad, 0, sizeof(int), s));
+    // the verdict: open, or (a wait of 0) called off from the start
+    const int off = 2;
+    if (m->res_wait_ms == 0.0) SEM_HIP(hipMemcpyAsync(&a.st->pad, &off, sizeof(int), hipMemcpyHostToDevice, s));
+    else SEM_HIP(hipMemsetAsync(&a.st->pad, 0, sizeof(int), s));
     SEM_HIP(launch_resident<T>(m->h.N, sh, a, s));
     hs = read_state(a.st, s);
-    return hs.pad == 1;
+    const bool stands = hs.pad == 1;
+    (stands ? m->res_runs : m->res_called_off)++;
+    return stands;
 }
 
 // Plain CG loop on precision T from the current r (x, p set by the caller);
@@ -1453,6 +1458,31 @@ sem_status sem_get_gs_config(const sem_mesh *m, int *kind, int *lattice_in_use)
         if (!m) fail(SEM_EINVAL, "sem_get_gs_config: null mesh");
         if (kind) *kind = m->gs_kind;
         if (lattice_in_use) *lattice_in_use = m->gs_lattice_ok && m->gs_kind != SEM_GS_PLAN;
+        return SEM_OK;
+    });
+}
+
+sem_status sem_set_resident_config(sem_mesh *m, int enable, double wait_ms)
+{
+    return guarded([&]() -> sem_status {
+        if (!m) fail(SEM_EINVAL, "sem_set_resident_config: null mesh");
+        if (enable != 0 && enable != 1) fail(SEM_EINVAL, "sem_set_resident_config: enable must be 0 or 1");
+        if (!(wait_ms <= 1000.0)) fail(SEM_EINVAL, "sem_set_resident_config: wait longer than 1000 ms");
+        m->res_enable = enable;
+        m->res_wait_ms = wait_ms;
+        return SEM_OK;
+    });
+}
+
+sem_status sem_get_resident_info(const sem_mesh *m, int *in_use, int64_t *runs, int64_t *called_off)
+{
+    return guarded([&]() -> sem_status {
+        if (!m) fail(SEM_EINVAL, "sem_get_resident_info: null mesh");
+        ResidentShape sh;
+        int cus = 0;
+        if (in_use) *in_use = resident_for<double>(m, sh, cus) ? 1 : 0;
+        if (runs) *runs = m->res_runs;
+        if (called_off) *called_off = m->res_called_off;
         return SEM_OK;
     });
 }

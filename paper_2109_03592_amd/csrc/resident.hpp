@@ -46,7 +46,8 @@ bool resident_shape(int N, int64_t E, size_t value_bytes, int cus, size_t lds_ca
 // Runs up to a.iters CG iterations from the state in *a.st (Jacobi, lattice
 // mesh), until convergence, breakdown or the limit.  st->pad must be 0; it is
 // 1 afterwards, or 2 when the workgroups did not meet within wait_ticks: then
-// neither the vectors nor the state were changed.
+// neither the vectors nor the state were changed.  (2 beforehand: it stays 2,
+// whatever the workgroups do.)
 template <typename T>
 hipError_t launch_resident(int N, const ResidentShape &s, const ResidentParams<T> &a, hipStream_t stream);
 hipError_t upload_resident_dtables(const double *d64, const float *d32, hipStream_t s);

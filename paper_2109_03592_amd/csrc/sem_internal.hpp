@@ -138,6 +138,9 @@ struct sem_mesh {
     uint64_t *res_words = nullptr;
     void *res_x = nullptr;
     uint32_t res_seq = 0;
+    int res_enable = 1;           // sem_set_resident_config
+    double res_wait_ms = -1.0;    // negative: the default; 0: no run stands
+    int64_t res_runs = 0, res_called_off = 0;
     double *partials = nullptr;   // reduction partials
     int64_t n_partials = 0;
     sem::PcgState *state = nullptr;  // [2]: FP64 solve, FP32 inner solve
