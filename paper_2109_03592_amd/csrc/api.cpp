@@ -916,19 +916,32 @@ static bool run_resident(sem_mesh *m, const ResidentShape &sh, int cus, int k, P
     return stands;
 }
 
+// The resident runs of one solve: where the mesh takes them, until one is
+// called off (a try costs the wait, and what kept its workgroups apart is
+// likely to be there at the solve's next restart or refinement step too).
+template <typename T>
+struct ResidentCg {
+    ResidentShape sh;
+    int cus = 0;
+    bool on;
+    ResidentCg(const sem_mesh *m, bool profile) : on(!profile && resident_for<T>(m, sh, cus)) {}
+    bool run(sem_mesh *m, int k, PcgState &hs, hipStream_t s)
+    {
+        on = on && run_resident<T>(m, sh, cus, k, hs, s);
+        return on;
+    }
+};
+
 // Plain CG loop on precision T from the current r (x, p set by the caller);
 // returns the final device state.
 template <typename T>
-static PcgState cg_loop(sem_mesh *m, double stop2, int limit, int poll, bool graph, hipStream_t s,
-                        Profiler *prof = nullptr)
+static PcgState cg_loop(sem_mesh *m, double stop2, int limit, int poll, bool graph, ResidentCg<T> &resident,
+                        hipStream_t s, Profiler *prof = nullptr)
 {
     pcg_start<T>(m, stop2, limit, s);
     PcgState hs = read_state(Prec<T>::st(m), s);
-    ResidentShape sh;
-    int cus = 0;
-    bool resident = !prof && resident_for<T>(m, sh, cus);
     while (!hs.done) {
-        if (resident && (resident = run_resident<T>(m, sh, cus, kResidentIters, hs, s))) continue;
+        if (resident.run(m, kResidentIters, hs, s)) continue;
         run_iterations<T>(m, poll, graph, s, prof);
         hs = read_state(Prec<T>::st(m), s);
     }
@@ -947,6 +960,7 @@ static sem_status solve_fp64(sem_mesh *m, const double *b, double *x, const sem_
     if (o.x0_given) SEM_HIP(hipMemcpyAsync(m->x64, x, sizeof(double) * nL, hipMemcpyDeviceToDevice, s));
     else SEM_HIP(hipMemsetAsync(m->x64, 0, sizeof(double) * nL, s));
     const int poll = std::max(1, o.poll_every);
+    ResidentCg<double> resident(m, o.profile != 0);
 
     if (o.fixed_iters > 0) {
         // throughput mode: exactly fixed_iters iterations from the current x
@@ -956,17 +970,11 @@ static sem_status solve_fp64(sem_mesh *m, const double *b, double *x, const sem_
         int left = o.fixed_iters;
         Profiler prof;
         prof.m = m;
-        ResidentShape sh;
-        int cus = 0;
-        bool resident = !o.profile && resident_for<double>(m, sh, cus);
         while (left > 0) {
-            if (resident) {
-                PcgState hs;
-                resident = run_resident<double>(m, sh, cus, left, hs, s);
-                if (resident) {
-                    left -= std::min(left, kResidentIters);
-                    continue;
-                }
+            PcgState hs;
+            if (resident.run(m, left, hs, s)) {
+                left -= std::min(left, kResidentIters);
+                continue;
             }
             const int k = std::min(left, poll);
             run_iterations<double>(m, k, o.use_graph != 0, s, o.profile ? &prof : nullptr);
@@ -1005,7 +1013,7 @@ static sem_status solve_fp64(sem_mesh *m, const double *b, double *x, const sem_
     for (;;) {
         if (have_x) true_residual(m, b, s, 1);
         else SEM_HIP(hipMemcpyAsync(m->r64, b, sizeof(double) * nL, hipMemcpyDeviceToDevice, s));
-        const PcgState hs = cg_loop<double>(m, stop2, o.max_iter - total, poll, o.use_graph != 0, s, pp);
+        const PcgState hs = cg_loop<double>(m, stop2, o.max_iter - total, poll, o.use_graph != 0, resident, s, pp);
         total += hs.iters;
         have_x = true;
         if (hs.done == 2) {
@@ -1060,6 +1068,7 @@ static sem_status solve_mixed(sem_mesh *m, const double *b, double *x, const sem
     else SEM_HIP(hipMemsetAsync(m->x64, 0, sizeof(double) * nL, s));
     const int poll = std::max(1, o.poll_every);
     const int inner_max = o.inner_max_iter > 0 ? o.inner_max_iter : o.max_iter;
+    ResidentCg<float> resident(m, o.profile != 0);
     sem_status status = SEM_OK;
     int total = 0, outer = 0;
     double rel = 0.0;
@@ -1090,7 +1099,7 @@ static sem_status solve_mixed(sem_mesh *m, const double *b, double *x, const sem
         SEM_HIP(hipMemsetAsync(m->x32, 0, sizeof(float) * nL, s));
         const int limit = std::min(inner_max, o.max_iter - total);
         const double eta = inner_tolerance(o, rel);
-        const PcgState hs = cg_loop<float>(m, eta * eta, limit, poll, o.use_graph != 0, s, pp);
+        const PcgState hs = cg_loop<float>(m, eta * eta, limit, poll, o.use_graph != 0, resident, s, pp);
         total += hs.iters;
         outer++;
         if (hs.iters == 0 && hs.done == 2) {

@@ -54,6 +54,23 @@ def test_called_off_run_changes_nothing(semlib, N, nel):
     m.close()
 
 
+def test_called_off_once_a_solve(semlib):
+    """A solve whose run was called off does not try again at each of its
+    restarts and refinement steps: every try costs the wait."""
+    print("case: resident tries of one solve", flush=True)
+    m = semlib.box_mesh(5, (4, 4, 4), vertices=SI.jittered_box_vertices((4, 4, 4), seed=5), with_fp32=True)
+    b = m.scatter(torch.from_numpy(SI.uniform_global_values(m.n_global, 3)).cuda())
+    m.set_resident(True, 0.0)
+    tries = 0
+    for precision in ("fp64", "mixed"):
+        x, r = m.solve(b, tol=1e-12, max_iter=20000, precision=precision, inner_tol=1e-2, raise_on_error=False)
+        if precision == "mixed":
+            assert r.outer_iterations >= 3
+        tries += 1
+        assert m.resident_info()["called_off"] == tries, (precision, r.outer_iterations)
+    m.close()
+
+
 def test_resident_config_is_checked(semlib):
     m = semlib.box_mesh(3, (2, 2, 2))
     for enable, wait in ((2, 1.0), (-1, 1.0), (1, 1001.0), (1, float("nan"))):
