@@ -799,7 +799,7 @@ static void pcg_start(sem_mesh *m, double stop2, int limit, hipStream_t s)
 // Compute units taken by resident runs in flight, per device: a run's
 // workgroups wait for each other, so all of them have to fit on the device
 // beside those of other threads' runs.  A run that does not fit waits for the
-// others (each holds its units for one launch, a few milliseconds), so what a
+// others (each holds its units for one launch, below 10 ms), so what a
 // solve returns does not depend on what runs beside it.
 struct ResidentUnits {
     std::mutex mu;
@@ -834,8 +834,6 @@ struct ResidentSeat {
     ResidentSeat &operator=(const ResidentSeat &) = delete;
 };
 
-// iterations of one launch, at most (a few milliseconds)
-constexpr int kResidentIters = 512;
 // longest wait of a resident run's workgroups for each other, in ticks of the
 // device's 100 MHz clock (20 ms)
 constexpr uint64_t kResidentWait = 2000000;
@@ -882,7 +880,7 @@ static bool run_resident(sem_mesh *m, const ResidentShape &sh, int cus, int k, P
 {
     if (!resident_space(m)) return false;
     ResidentSeat seat(m->device, sh.nwg, cus);
-    if (m->res_seq == 0 || m->res_seq > UINT32_MAX - 2 * kResidentIters) {
+    if (m->res_seq == 0 || m->res_seq > UINT32_MAX - 2 * kResidentMaxIters) {
         SEM_HIP(hipMemsetAsync(m->res_words, 0, sizeof(uint64_t) * kResidentWords, s));
         m->res_seq = 0;
     }
@@ -902,7 +900,7 @@ static bool run_resident(sem_mesh *m, const ResidentShape &sh, int cus, int k, P
     a.st = Prec<T>::st(m);
     a.words = m->res_words;
     a.seq = m->res_seq;
-    a.iters = std::min(k, kResidentIters);
+    a.iters = std::min(k, sh.iters);
     a.wait_ticks = m->res_wait_ms < 0.0 ? kResidentWait : (uint64_t)(m->res_wait_ms * 1e5);
     m->res_seq += (uint32_t)a.iters;
     // the verdict: open, or (a wait of 0) called off from the start
@@ -941,7 +939,7 @@ static PcgState cg_loop(sem_mesh *m, double stop2, int limit, int poll, bool gra
     pcg_start<T>(m, stop2, limit, s);
     PcgState hs = read_state(Prec<T>::st(m), s);
     while (!hs.done) {
-        if (resident.run(m, kResidentIters, hs, s)) continue;
+        if (resident.run(m, resident.sh.iters, hs, s)) continue;
         run_iterations<T>(m, poll, graph, s, prof);
         hs = read_state(Prec<T>::st(m), s);
     }
@@ -973,7 +971,7 @@ static sem_status solve_fp64(sem_mesh *m, const double *b, double *x, const sem_
         while (left > 0) {
             PcgState hs;
             if (resident.run(m, left, hs, s)) {
-                left -= std::min(left, kResidentIters);
+                left -= std::min(left, resident.sh.iters);
                 continue;
             }
             const int k = std::min(left, poll);

@@ -463,6 +463,12 @@ bool resident_shape(int N, int64_t E, size_t value_bytes, int cus, size_t lds_ca
     s.nwg = (int)((E + epw - 1) / epw);
     s.threads = (int)((epw * P2 + 63) / 64 * 64);
     s.lds = s.g_in_lds ? with_g : without;
+    // A launch holds its compute units to its end, and other runs wait for
+    // them: below 10 ms at the measured 12 to 19 us an iteration with the
+    // factors on chip, and where they are read at 17 to 19 (up to 128 KB a
+    // workgroup), 25 to 34 (up to 200 KB) and 45 to 64 us.
+    const size_t reads = s.g_in_lds ? 0 : (size_t)epw * 6 * P3 * value_bytes;
+    s.iters = reads <= 128 * 1024 ? kResidentMaxIters : (reads <= 200 * 1024 ? 256 : 128);
     return true;
 }
 

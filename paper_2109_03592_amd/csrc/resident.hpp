@@ -14,6 +14,7 @@ constexpr int kResidentMaxWg = 256;  // workgroups of a resident run, at most
 // tagged words the workgroups exchange: two per workgroup for <p, A p>, four
 // for <r, r> and <r, z>
 constexpr int kResidentWords = 6 * kResidentMaxWg;
+constexpr int kResidentMaxIters = 512;  // iterations of a launch, at most
 
 struct ResidentShape {
     int epw = 0;      // elements per workgroup (one workgroup per compute unit)
@@ -21,6 +22,7 @@ struct ResidentShape {
     int threads = 0;
     size_t lds = 0;   // dynamic LDS bytes
     bool g_in_lds = false;  // the factors stay in LDS, else they are read every iteration
+    int iters = 0;          // iterations of one launch, at most
 };
 
 template <typename T>
