@@ -796,11 +796,17 @@ static void pcg_start(sem_mesh *m, double stop2, int limit, hipStream_t s)
 }
 
 // --- resident CG of a small mesh ---------------------------------------------
-// Compute units taken by resident runs in flight, per device: a run's
-// workgroups wait for each other, so all of them have to fit on the device
-// beside those of other threads' runs.  A run that does not fit waits for the
-// others (each holds its units for one launch, below 10 ms), so what a
-// solve returns does not depend on what runs beside it.
+// Compute units of one XCD taken by resident runs in flight, per device: a
+// run's workgroups wait for each other, so all of them have to fit on the
+// device beside those of other threads' runs, on every XCD -- a launch's
+// workgroups go to the 8 XCDs in turn, whichever is first, so none gets more
+// than an eighth of them rounded up.  A run that does not fit waits for the
+// others (each holds its units for one launch, below 10 ms), so this process's
+// resident runs do not call each other off.  Other kernels and other processes
+// can keep a run's workgroups apart: then it is called off, and the general
+// iteration that goes on sums its dot products in another order, which changes
+// the result at rounding level.
+constexpr int kXcds = 8;
 struct ResidentUnits {
     std::mutex mu;
     std::condition_variable cv;
@@ -813,12 +819,12 @@ static ResidentUnits &resident_units()
 }
 struct ResidentSeat {
     int dev, n;
-    ResidentSeat(int device, int want, int cus) : dev(device), n(want)
+    ResidentSeat(int device, int nwg, int cus) : dev(device), n((nwg + kXcds - 1) / kXcds)
     {
         ResidentUnits &u = resident_units();
         std::unique_lock<std::mutex> lock(u.mu);
         if ((int)u.used.size() <= dev) u.used.resize(dev + 1, 0);
-        u.cv.wait(lock, [&] { return u.used[dev] == 0 || u.used[dev] + n <= cus; });
+        u.cv.wait(lock, [&] { return u.used[dev] == 0 || u.used[dev] + n <= cus / kXcds; });
         u.used[dev] += n;
     }
     ~ResidentSeat()

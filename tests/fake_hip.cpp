@@ -2,12 +2,16 @@
 // CPU: device memory is host memory, copies and fills are done, kernels are
 // only recorded.  Loaded with global symbols before libsem.so, whose HIP calls
 // it answers; an allocation can be made to fail, as on a full device.
+#include <algorithm>
+#include <chrono>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <set>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "resident.hpp"
@@ -23,11 +27,13 @@ struct Launch {
 std::map<const void *, std::string> names;
 std::set<void *> blocks;
 std::vector<Launch> launches;
-hipError_t last = hipSuccess;  // kept until it is read, as the runtime does
+thread_local hipError_t last = hipSuccess;  // kept until it is read, as the runtime does
 int fail_in = -1;              // allocations until one fails
 int null_uses = 0;             // copies, fills and kernels given no memory
 int verdict = 0;               // what a resident run leaves in its state
 int64_t allocated = 0, copied = 0;
+int hold_ms = 0, in_flight = 0, max_in_flight = 0;  // resident runs
+std::mutex mu;  // of what follows from launches and allocations
 
 hipError_t put(hipError_t e)
 {
@@ -52,7 +58,13 @@ void fake_set_verdict(int v) { verdict = v; }
 int fake_null_uses() { return null_uses; }
 int64_t fake_allocated() { return allocated; }
 int64_t fake_copied() { return copied; }
-void fake_clear() { launches.clear(); }
+void fake_hold_ms(int ms) { hold_ms = ms; }
+int fake_max_in_flight() { return max_in_flight; }
+void fake_clear()
+{
+    launches.clear();
+    max_in_flight = 0;
+}
 int fake_launches() { return (int)launches.size(); }
 const char *fake_name(int i) { return launches[i].name.c_str(); }
 unsigned fake_grid(int i) { return launches[i].grid; }
@@ -95,8 +107,16 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
 }
 hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, hipStream_t)
 {
+    std::unique_lock<std::mutex> lock(mu);
     Launch l{names[f], g.x, b.x, lds, 0, false};
     if (l.name.find("resident_kernel") != std::string::npos) {
+        if (hold_ms) {  // the run takes its time
+            max_in_flight = std::max(max_in_flight, ++in_flight);
+            lock.unlock();
+            std::this_thread::sleep_for(std::chrono::milliseconds(hold_ms));
+            lock.lock();
+            --in_flight;
+        }
         if (l.name.find("resident_kernelId") != std::string::npos) resident<double>(l, args);
         else resident<float>(l, args);
     }
@@ -117,6 +137,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t ld
 hipError_t hipMalloc(void **p, size_t bytes)
 {
     *p = nullptr;
+    std::lock_guard<std::mutex> lock(mu);
     if (fail_in >= 0 && fail_in-- == 0) return put(hipErrorOutOfMemory);
     *p = std::calloc(1, bytes);
     blocks.insert(*p);
@@ -125,6 +146,7 @@ hipError_t hipMalloc(void **p, size_t bytes)
 }
 hipError_t hipFree(void *p)
 {
+    std::lock_guard<std::mutex> lock(mu);
     if (p && blocks.erase(p)) std::free(p);
     return hipSuccess;
 }

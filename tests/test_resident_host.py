@@ -1,5 +1,5 @@
 """Host side of the resident CG on the CPU (fake_hip.cpp): how many iterations
-a launch takes."""
+a launch takes, and which runs of several threads are in flight together."""
 import pytest
 
 import fakehip
@@ -27,4 +27,32 @@ def test_iterations_of_a_launch(runtime):
             got = [fake.fake_iters(i) for i in launches("resident_kernel")]
             assert got == want, (N, nel, got)
             lib.sem_free(m)
+        """)
+
+
+def test_runs_in_flight_fit_every_xcd(runtime):
+    """The workgroups of a launch go to the 8 XCDs in turn, 32 compute units
+    each: 129 and 127 workgroups fit the device's 256 but put 17 + 16 on one
+    XCD, so one run waits for the other; 128 and 128 run side by side."""
+    fakehip.run(runtime, """
+        import threading
+        fake.fake_set_verdict(1)
+        fake.fake_hold_ms(300)
+        def flight(sizes):
+            ms = [mesh(3, nel) for nel in sizes]
+            def work(m, info):
+                b, x = np.ones(info.n_local), np.zeros(info.n_local)
+                o = opts(fixed_iters=1)
+                L.check(lib.sem_pcg_solve(m, b.ctypes.data, x.ctypes.data, C.byref(o), None, None), "solve")
+            fake.fake_clear()
+            th = [threading.Thread(target=work, args=m) for m in ms]
+            for t in th:
+                t.start()
+            for t in th:
+                t.join()
+            assert len(launches("resident_kernel")) == len(sizes)
+            return fake.fake_max_in_flight(), sorted(fake.fake_grid(i) for i in launches("resident_kernel"))
+        assert flight([(1, 1, 257), (1, 1, 127)]) == (1, [127, 129])
+        assert flight([(1, 1, 128), (1, 1, 128)]) == (2, [128, 128])
+        assert flight([(1, 1, 64), (1, 1, 64), (1, 1, 56), (1, 1, 72)]) == (4, [56, 64, 64, 72])
         """)
