@@ -18,11 +18,11 @@
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
-#include <utility>
 #include <vector>
 
 #include "batch.hpp"
 #include "coarse.hpp"
+#include "coarse_tiles.hpp"
 #include "kernels.hpp"
 #include "lattice.hpp"
 #include "operator.hpp"
@@ -455,87 +455,61 @@ void coarse_free(CoarseSpace *C)
     delete C;
 }
 
+// The lists of the tiles, one workgroup each.  They follow from the lattice, so
+// nothing is searched or sent: on the 48x48x96 pipe (588 tiles) this launch and
+// its allocations take 0.2 ms where a walk of the host over the rows of A0 and
+// the copy of its 110 MB of lists took 50.
+__global__ __launch_bounds__(256) void tile_lists_kernel(TileGeom g, const double *__restrict__ d0inv,
+                                                         int32_t *__restrict__ level, int32_t *__restrict__ vert,
+                                                         int32_t *__restrict__ corner, int16_t *__restrict__ col)
+{
+    __shared__ TileSets s;
+    const int64_t t = blockIdx.x;
+    const int tid = threadIdx.x;
+    if (tid == 0) tile_sets(g, t, s);
+    __syncthreads();
+    if (tid < kTileRings) level[t * kTileRings + tid] = s.count[tid];
+    for (int i = tid; i < s.count[g.depth]; i += 256) tile_vertex(g, s, t, i, d0inv, vert, corner, col);
+    tile_padding(g, s, t, tid, 256, vert, corner, col);
+}
+
 // The tiles of the vertex lattice (extents vd).  The box edge is the smallest
 // from 3 on that gives at most a workgroup per compute unit: a smaller box
 // lists fewer vertices, which is what a workgroup's time goes by, a larger one
 // repeats less (3: 27 listed vertices per vertex, 8: 5.4).  Preconditioner of
 // 16^3 elements with edge 2, 3 and 4: 31.0, 31.0 and 32.8 us.
-static void build_tiles(CoarseSpace *C, const int vd[3], const std::vector<int32_t> &v_off,
-                        const std::vector<int32_t> &v_idx, const std::vector<int32_t> &off,
-                        const std::vector<int32_t> &col, hipStream_t s)
+static void build_tiles(CoarseSpace *C, const HostMesh &h, const int vd[3], hipStream_t s)
 {
-    int nt[3];
-    for (int edge = 3; edge <= kTileEdge; ++edge) {
-        for (int a = 0; a < 3; ++a) nt[a] = (vd[a] + edge - 1) / edge;
-        if ((int64_t)nt[0] * nt[1] * nt[2] <= 256) break;
+    static_assert(kTileRings == kTileSteps + 1, "a ring for each product of a launch");
+    TileGeom g{};
+    for (int a = 0; a < 3; ++a) {
+        g.vd[a] = vd[a];
+        g.nel[a] = h.nel[a];
+        g.periodic[a] = h.periodic[a] ? 1 : 0;
     }
-    const int64_t n = (int64_t)nt[0] * nt[1] * nt[2];
-    const int depth = std::min(kTileSteps, C->k - 1);
+    for (int edge = 3; edge <= kTileEdge; ++edge) {
+        for (int a = 0; a < 3; ++a) g.nt[a] = (vd[a] + edge - 1) / edge;
+        if ((int64_t)g.nt[0] * g.nt[1] * g.nt[2] <= 256) break;
+    }
+    const int64_t n = (int64_t)g.nt[0] * g.nt[1] * g.nt[2];
+    g.depth = std::min(kTileSteps, C->k - 1);
+    tile_strides(g);
+    if (g.core > kTileCore || g.rows > kTileRows || g.verts > kTileVerts)
+        fail(SEM_EINVAL, "sem_set_coarse: a tile exceeds its bounds");
     CoarseTiles &T = C->tiles;
     T.n = (int)n;
-    std::vector<std::vector<int32_t>> list((size_t)n);
-    std::vector<int32_t> level, where((size_t)C->nvert, -1);
-    for (int64_t t = 0; t < n; ++t) {
-        const int64_t at[3] = {t % nt[0], (t / nt[0]) % nt[1], t / ((int64_t)nt[0] * nt[1])};
-        int lo[3], hi[3];
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = (int)(at[a] * vd[a] / nt[a]);
-            hi[a] = (int)((at[a] + 1) * vd[a] / nt[a]);
-        }
-        std::vector<int32_t> &vert = list[(size_t)t];
-        auto add = [&](int32_t v) {
-            if (where[v] >= 0) return;
-            where[v] = (int32_t)vert.size();
-            vert.push_back(v);
-        };
-        for (int z = lo[2]; z < hi[2]; ++z)
-            for (int y = lo[1]; y < hi[1]; ++y)
-                for (int x = lo[0]; x < hi[0]; ++x) add((int32_t)(x + vd[0] * (y + (int64_t)vd[1] * z)));
-        int32_t cnt[kTileSteps + 1];
-        cnt[0] = (int32_t)vert.size();
-        for (int q = 1; q <= kTileSteps; ++q) {
-            for (int32_t h = q > 1 ? cnt[q - 2] : 0; q <= depth && h < cnt[q - 1]; ++h)
-                for (int32_t e = off[vert[h]]; e < off[vert[h] + 1]; ++e) add(col[e]);
-            std::sort(vert.begin() + cnt[q - 1], vert.end());  // runs along x: neighbouring values
-            cnt[q] = (int32_t)vert.size();
-        }
-        for (const int32_t v : vert) where[v] = -1;
-        level.insert(level.end(), cnt, cnt + kTileSteps + 1);
-        T.core = std::max(T.core, cnt[0]);
-        if (depth > 0) T.rows = std::max(T.rows, cnt[depth - 1]);
-        T.verts = std::max(T.verts, cnt[depth]);
-    }
-    if (T.core > kTileCore || T.rows > kTileRows || T.verts > kTileVerts)
-        fail(SEM_EINVAL, "sem_set_coarse: a tile exceeds its bounds");
-    std::vector<int32_t> vert((size_t)n * T.verts), corner((size_t)n * T.verts * 8, -1);
-    std::vector<int16_t> lcol((size_t)n * T.rows * 32, -1);
-    for (int64_t t = 0; t < n; ++t) {
-        const std::vector<int32_t> &l = list[(size_t)t];
-        for (size_t h = 0; h < l.size(); ++h) where[l[h]] = (int32_t)h;
-        for (size_t h = 0; h < (size_t)T.verts; ++h) {
-            const int32_t v = h < l.size() ? l[h] : l[0];
-            vert[(size_t)t * T.verts + h] = v;
-            if (h >= l.size()) continue;
-            for (int32_t q = v_off[v]; q < v_off[v + 1]; ++q)
-                corner[((size_t)t * T.verts + h) * 8 + (q - v_off[v])] = v_idx[q];
-            if (depth == 0 || (int32_t)h >= level[(size_t)t * (kTileSteps + 1) + depth - 1]) continue;
-            const size_t at = (size_t)t * T.rows + h;
-            for (int32_t x = 0; x < off[v + 1] - off[v]; ++x)
-                lcol[at * 32 + (x & 7) * 4 + (x >> 3)] = (int16_t)where[col[off[v] + x]];
-        }
-        for (const int32_t v : l) where[v] = -1;
-    }
-    auto put = [&](auto &v) {
-        using X = typename std::decay_t<decltype(v)>::value_type;
-        X *p = cmalloc<X>(C, v.size());
-        if (!v.empty()) SEM_HIP(hipMemcpyAsync(p, v.data(), sizeof(X) * v.size(), hipMemcpyHostToDevice, s));
-        return p;
-    };
-    T.level = put(level);
-    T.vert = put(vert);
-    T.corner = put(corner);
-    T.col = put(lcol);
-    SEM_HIP(hipStreamSynchronize(s));  // the vectors go
+    T.verts = g.verts;
+    T.rows = g.rows;
+    T.core = g.core;
+    int32_t *level = cmalloc<int32_t>(C, (size_t)n * kTileRings), *vert = cmalloc<int32_t>(C, (size_t)n * T.verts),
+            *corner = cmalloc<int32_t>(C, (size_t)n * T.verts * 8);
+    int16_t *col = cmalloc<int16_t>(C, (size_t)n * T.rows * 32);
+    hipLaunchKernelGGL(tile_lists_kernel, dim3((unsigned)n), dim3(256), 0, s, g, C->d0inv, level, vert, corner, col);
+    SEM_HIP(hipGetLastError());
+    T.level = level;
+    T.vert = vert;
+    T.corner = corner;
+    T.col = col;
 }
 
 CoarseSpace *coarse_build(sem_mesh *m, int k, double frac, hipStream_t s)
@@ -610,39 +584,39 @@ CoarseSpace *coarse_build(sem_mesh *m, int k, double frac, hipStream_t s)
             SEM_HIP(hipFree(w));
             SEM_HIP(hipFree(dE8));
         }
-        // A0 rows: sum of the element blocks of the vertex's corners, ascending
-        std::vector<int32_t> off((size_t)C->nvert + 1, 0), col;
-        std::vector<double> val, diag((size_t)C->nvert, 0.0);
-        col.reserve((size_t)C->nvert * 27);
-        val.reserve((size_t)C->nvert * 27);
-        // entries of a row are summed in the order of its element corners
-        std::vector<std::pair<int32_t, double>> row;
-        row.reserve(64);
+        // A0 rows: sum of the element blocks of the vertex's corners, ascending,
+        // at the places of the row's columns (ascending; the lattice gives them)
+        std::vector<double> rows((size_t)C->nvert * 32, 0.0), diag((size_t)C->nvert, 0.0);
+        auto entry = [&](int64_t v, int x) -> double & { return rows[(size_t)v * 32 + (x & 7) * 4 + (x >> 3)]; };
+        auto columns = [&](int64_t v, AxisSet (&set)[3], int (&at)[3]) {
+            at[0] = (int)(v % vd[0]);
+            at[1] = (int)(v / vd[0] % vd[1]);
+            at[2] = (int)(v / ((int64_t)vd[0] * vd[1]));
+            for (int a = 0; a < 3; ++a) set[a] = axis_set(at[a], at[a] + 1, 1, vd[a], h.periodic[a]);
+        };
+        C->n_coarse = C->nnz = 0;
         for (int64_t v = 0; v < C->nvert; ++v) {
-            row.clear();
+            AxisSet set[3];
+            int at[3], place[3][3];  // place of the neighbour one down, of the vertex itself, of the one up
+            columns(v, set, at);
+            for (int a = 0; a < 3; ++a)
+                for (int d = 0; d < 3; ++d) place[a][d] = axis_below(set[a], (at[a] + d - 1 + vd[a]) % vd[a]);
+            const int len = set[0].len * set[1].len * set[2].len;
+            double row[27] = {0.0};
             for (int32_t q = v_off[v]; q < v_off[v + 1]; ++q) {
-                const int64_t e = v_idx[q] / 8, cr = v_idx[q] % 8;
-                for (int c = 0; c < 8; ++c) row.emplace_back(evert[e * 8 + c], E8[e * 64 + cr * 8 + c]);
-            }
-            std::stable_sort(row.begin(), row.end(),
-                             [](const std::pair<int32_t, double> &x, const std::pair<int32_t, double> &y) {
-                                 return x.first < y.first;
-                             });
-            const size_t start = col.size();
-            for (size_t q = 0; q < row.size(); ++q) {
-                if (q == 0 || row[q].first != row[q - 1].first) {
-                    col.push_back(row[q].first);
-                    val.push_back(row[q].second);
-                } else {
-                    val.back() += row[q].second;
+                const int cr = v_idx[q] % 8;
+                const double *block = &E8[(size_t)v_idx[q] * 8];
+                for (int c = 0; c < 8; ++c) {
+                    const int x = place[0][(c & 1) - (cr & 1) + 1],
+                              y = place[1][((c >> 1) & 1) - ((cr >> 1) & 1) + 1], z = place[2][(c >> 2) - (cr >> 2) + 1];
+                    row[x + set[0].len * (y + set[1].len * z)] += block[c];
                 }
-                if (row[q].first == (int32_t)v) diag[v] = val.back();
             }
-            if (!(diag[v] > 0.0)) {  // not a coarse unknown: empty row
-                col.resize(start);
-                val.resize(start);
-            }
-            off[v + 1] = (int32_t)col.size();
+            diag[v] = row[place[0][1] + set[0].len * (place[1][1] + set[1].len * place[2][1])];
+            if (!(diag[v] > 0.0)) continue;  // not a coarse unknown: empty row
+            for (int x = 0; x < len; ++x) entry(v, x) = row[x];
+            C->n_coarse++;
+            C->nnz += len;
         }
         // vertices whose masked hat is zero are not coarse unknowns: drop their columns
         std::vector<double> d0inv((size_t)C->nvert, 0.0);
@@ -651,25 +625,26 @@ CoarseSpace *coarse_build(sem_mesh *m, int k, double frac, hipStream_t s)
         double bmax = 0.0;
         for (int64_t v = 0; v < C->nvert; ++v) {
             if (!(diag[v] > 0.0)) continue;
+            AxisSet set[3];
+            int at[3];
+            columns(v, set, at);
+            const int len = set[0].len * set[1].len * set[2].len;
             double sabs = 0.0;
-            for (int32_t q = off[v]; q < off[v + 1]; ++q) {
-                if (!(diag[col[q]] > 0.0)) val[q] = 0.0;
-                sabs += std::fabs(val[q]);
+            for (int x = 0; x < len; ++x) {
+                double &a = entry(v, x);
+                if (C->n_coarse < C->nvert) {
+                    const int64_t u = axis_at(set[0], x % set[0].len) +
+                                      vd[0] * (axis_at(set[1], x / set[0].len % set[1].len) +
+                                               (int64_t)vd[1] * axis_at(set[2], x / (set[0].len * set[1].len)));
+                    if (!(diag[u] > 0.0)) a = 0.0;
+                }
+                sabs += std::fabs(a);
             }
             bmax = std::max(bmax, sabs * d0inv[v]);
         }
         if (!(bmax > 0.0)) fail(SEM_EINVAL, "sem_set_coarse: the coarse operator is zero");
         C->b = bmax;
         C->a = frac * bmax;
-        C->n_coarse = 0;
-        for (int64_t v = 0; v < C->nvert; ++v) C->n_coarse += diag[v] > 0.0;
-        C->nnz = (int64_t)col.size();
-        std::vector<double> rows((size_t)C->nvert * 32, 0.0);
-        for (int64_t v = 0; v < C->nvert; ++v)
-            for (int32_t q = off[v]; q < off[v + 1]; ++q) {
-                const int32_t x = q - off[v];
-                rows[(size_t)v * 32 + (x & 7) * 4 + (x >> 3)] = val[q];
-            }
         C->a_val = cmalloc<double>(C, rows.size());
         C->d0inv = cmalloc<double>(C, d0inv.size());
         SEM_HIP(hipMemcpyAsync(C->a_val, rows.data(), sizeof(double) * rows.size(), hipMemcpyHostToDevice, s));
@@ -693,7 +668,7 @@ CoarseSpace *coarse_build(sem_mesh *m, int k, double frac, hipStream_t s)
             C->d[q] = cmalloc<double>(C, C->nvert);
         }
         C->partial8 = cmalloc<double>(C, (size_t)E * 8);
-        build_tiles(C, vd, v_off, v_idx, off, col, s);
+        build_tiles(C, h, vd, s);
         C->dot_blocks = std::min(C->tiles.n, kMaxCoarseDotBlocks);
         SEM_HIP(hipMemsetAsync(C->z0, 0, sizeof(double) * C->nvert, s));
         SEM_HIP(hipStreamSynchronize(s));

@@ -32,6 +32,7 @@ int fail_in = -1;              // allocations until one fails
 int null_uses = 0;             // copies, fills and kernels given no memory
 int verdict = 0;               // what a resident run leaves in its state
 int64_t allocated = 0, copied = 0;
+double fill = 0.0;             // what new device memory holds
 int hold_ms = 0, in_flight = 0, max_in_flight = 0;  // resident runs
 std::mutex mu;  // of what follows from launches and allocations
 
@@ -58,6 +59,7 @@ void fake_set_verdict(int v) { verdict = v; }
 int fake_null_uses() { return null_uses; }
 int64_t fake_allocated() { return allocated; }
 int64_t fake_copied() { return copied; }
+void fake_fill(double v) { fill = v; }
 void fake_hold_ms(int ms) { hold_ms = ms; }
 int fake_max_in_flight() { return max_in_flight; }
 void fake_clear()
@@ -139,7 +141,8 @@ hipError_t hipMalloc(void **p, size_t bytes)
     *p = nullptr;
     std::lock_guard<std::mutex> lock(mu);
     if (fail_in >= 0 && fail_in-- == 0) return put(hipErrorOutOfMemory);
-    *p = std::calloc(1, bytes);
+    *p = std::malloc(bytes + 8);
+    for (size_t q = 0; q < bytes + 8 - 7; q += 8) std::memcpy(static_cast<char *>(*p) + q, &fill, 8);
     blocks.insert(*p);
     allocated += (int64_t)bytes;
     return hipSuccess;
