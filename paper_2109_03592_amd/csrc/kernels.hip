@@ -475,7 +475,6 @@ __global__ __launch_bounds__(1024) void reduce_scalar_kernel(const double *__res
 }
 
 // sigma = <p, A p>; alpha = rho / sigma (breakdown when sigma <= 0 or not finite)
-// alpha = rho / sigma, or a breakdown
 __device__ inline void set_alpha(PcgState *st, double sigma)
 {
     st->sigma = sigma;

@@ -36,6 +36,23 @@ __device__ inline void block_reduce_store(double (&v)[NV], double *dst, int stri
     }
 }
 
+// s + s of the lane that the DPP control CTRL names, within rows of 16 lanes, on
+// the vector unit (a fifth of the latency of a cross-lane shuffle through LDS)
+template <int CTRL>
+__device__ inline double dpp_add(double s)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(s), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(s), CTRL, 0xf, 0xf, true);
+    return s + __hiloint2double(hi, lo);
+}
+// sum over eight lanes: pairs, fours, the other four
+__device__ inline double sum8(double s)
+{
+    s = dpp_add<0xb1>(s);     // quad_perm [1, 0, 3, 2]
+    s = dpp_add<0x4e>(s);     // quad_perm [2, 3, 0, 1]
+    return dpp_add<0x141>(s); // row_half_mirror
+}
+
 // 1/mult exactly: a node's copies are one or two along each axis, so its
 // multiplicity is a power of two and the reciprocal only sets an exponent
 __device__ inline double inv_mult(uint8_t m)
@@ -464,7 +481,7 @@ __device__ inline void ax_tile_planes(const LaneRows<T, N> &R, const T *__restri
     // plane k is worked on, so that their latency overlaps a whole plane's
     // barriers and LDS products.  h1 loaded where it multiplies, and h2 B after
     // the last plane, cost the Helmholtz operator one latency per plane: N = 9,
-    // 13.8M points 270 -> 228 us (floor 178), N = 12 385 -> 295 us.  A second
+    // 13.8M points 270 -> 228 us (floor 178), N = 12 385 -> 306 us.  A second
     // plane ahead gains nothing more (N = 9: 232 us) and takes registers.
     T gn[6], hn = 0, bn = 0;
 #pragma unroll

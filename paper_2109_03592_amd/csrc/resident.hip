@@ -35,30 +35,19 @@ __device__ inline T ld_dev(const T *p) { return __hip_atomic_load(p, __ATOMIC_RE
 template <typename T>
 __device__ inline void st_dev(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// Sum over the wavefront, the same bits in every lane.  Within rows of 16
-// lanes through DPP moves and across the rows through scalar reads: a fifth of
-// the latency of six cross-lane shuffles through LDS, and it is paid four
-// times per iteration.
-template <int CTRL>
-__device__ inline double dpp_add(double s)
-{
-    const long long b = __double_as_longlong(s);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
-    return s + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
 __device__ inline double read_lane(double s, int lane)
 {
     const long long b = __double_as_longlong(s);
     const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
+// Sum over the wavefront, the same bits in every lane.  Within rows of 16
+// lanes through DPP moves and across the rows through scalar reads: a fifth of
+// the latency of six cross-lane shuffles through LDS, and it is paid four
+// times per iteration.
 __device__ inline double wave_total(double s)
 {
-    s = dpp_add<0xb1>(s);   // quad_perm [1, 0, 3, 2]
-    s = dpp_add<0x4e>(s);   // quad_perm [2, 3, 0, 1]
-    s = dpp_add<0x141>(s);  // row_half_mirror
-    s = dpp_add<0x140>(s);  // row_mirror
+    s = dpp_add<0x140>(sum8(s));  // row_mirror
     return (read_lane(s, 0) + read_lane(s, 16)) + (read_lane(s, 32) + read_lane(s, 48));
 }
 
