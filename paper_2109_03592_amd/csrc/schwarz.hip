@@ -279,7 +279,10 @@ constexpr int kColElems = 256 / ((N + 1) * (N + 1)) > 0 ? 256 / ((N + 1) * (N + 
 // at a copy's rate) and is bound by its partly filled loads.  Not kept: more
 // loads in flight per lane (half a column 111 us, a whole one 116 us; the
 // waves that fit fell from 8 to 5 and 3 per SIMD).
-template <int N, bool COARSE>
+// COLUMN false: one lane per node, plane blockIdx.y.  On a mesh whose columns
+// leave compute units idle, a lane's planes are a chain of memory latencies:
+// 64 elements of N = 7 3.8 us instead of 6.7, M^-1 r 11.9 instead of 15.0.
+template <int N, bool COARSE, bool COLUMN>
 __global__ __launch_bounds__(256) void assemble_kernel(int64_t E, Lattice L, const double *__restrict__ zext,
                                                        const int32_t *__restrict__ evert,
                                                        const double *__restrict__ z0, const double *__restrict__ cq,
@@ -341,7 +344,8 @@ __global__ __launch_bounds__(256) void assemble_kernel(int64_t E, Lattice L, con
     const bool zl = has_left(L, 2, pos[2]), zr = has_right(L, 2, pos[2]);
     const int64_t zlo = wrap_lo(2), zhi = wrap_hi(2);
 #pragma unroll
-    for (int k = 0; k < P; ++k) {
+    for (int kk = 0; kk < (COLUMN ? P : 1); ++kk) {
+        const int k = COLUMN ? kk : (int)blockIdx.y;
         double val[8];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -667,16 +671,28 @@ void schwarz_assemble(sem_mesh *m, double *z, bool add_coarse, const PcgState *s
         SEM_HIP(hipGetLastError());
         return;
     }
+    // a lane per node up to where its workgroups (N + 1 times those of the
+    // columns) fill the device and repeat the columns' work for nothing: M^-1 r,
+    // us per node and per column, N = 7 with 183 workgroups of columns 16.7 and
+    // 17.9, with 250 18.2 and 17.3; N = 11 216 21.2 and 23.8, 512 26.1 and 23.9;
+    // N = 3 108 11.3 and 12.3, 172 13.5 and 13.3
+    const unsigned per_node = m->h.N <= 4 ? 128 : 208;
+#define SEM_ASM_RUN(n, coarse, column, grid)                                                                        \
+    hipLaunchKernelGGL((assemble_kernel<n, coarse, column>), grid, dim3(256), 0, s, E, L, Z->zext, ev, z0, cq, z, st)
 #define SEM_ASM(n)                                                                                                 \
     do {                                                                                                           \
-        const dim3 grid((unsigned)((E + kColElems<n> - 1) / kColElems<n>));                                        \
-        if (add_coarse)                                                                                            \
-            hipLaunchKernelGGL((assemble_kernel<n, true>), grid, dim3(256), 0, s, E, L, Z->zext, ev, z0, cq, z, st); \
-        else                                                                                                       \
-            hipLaunchKernelGGL((assemble_kernel<n, false>), grid, dim3(256), 0, s, E, L, Z->zext, ev, z0, cq, z, st); \
+        const unsigned wgs = (unsigned)((E + kColElems<n> - 1) / kColElems<n>);                                    \
+        if (wgs <= per_node) {                                                                                     \
+            if (add_coarse) SEM_ASM_RUN(n, true, false, dim3(wgs, n + 1));                                         \
+            else SEM_ASM_RUN(n, false, false, dim3(wgs, n + 1));                                                   \
+        } else {                                                                                                   \
+            if (add_coarse) SEM_ASM_RUN(n, true, true, dim3(wgs));                                                 \
+            else SEM_ASM_RUN(n, false, true, dim3(wgs));                                                           \
+        }                                                                                                          \
     } while (0)
     SEM_SCHWARZ_ORDER_SWITCH(m->h.N, SEM_ASM)
 #undef SEM_ASM
+#undef SEM_ASM_RUN
     SEM_HIP(hipGetLastError());
 }
 

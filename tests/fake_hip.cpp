@@ -19,7 +19,7 @@
 namespace {
 struct Launch {
     std::string name;
-    unsigned grid, block;
+    unsigned grid, grid_y, block;
     size_t lds;
     int iters;        // resident runs
     bool has_scratch;
@@ -70,6 +70,7 @@ void fake_clear()
 int fake_launches() { return (int)launches.size(); }
 const char *fake_name(int i) { return launches[i].name.c_str(); }
 unsigned fake_grid(int i) { return launches[i].grid; }
+unsigned fake_grid_y(int i) { return launches[i].grid_y; }
 unsigned fake_block(int i) { return launches[i].block; }
 int fake_iters(int i) { return launches[i].iters; }
 int fake_has_scratch(int i) { return launches[i].has_scratch; }
@@ -110,7 +111,7 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
 hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, hipStream_t)
 {
     std::unique_lock<std::mutex> lock(mu);
-    Launch l{names[f], g.x, b.x, lds, 0, false};
+    Launch l{names[f], g.x, g.y, b.x, lds, 0, false};
     if (l.name.find("resident_kernel") != std::string::npos) {
         if (hold_ms) {  // the run takes its time
             max_in_flight = std::max(max_in_flight, ++in_flight);

@@ -47,3 +47,22 @@ def test_elements_per_workgroup(runtime):
             assert got == [want], (N, nel, use, got, want)
             lib.sem_free(m)
         """)
+
+
+def test_schwarz_assembly_lanes(runtime):
+    """The sum of the local solves takes a lane per node while its columns
+    leave the device idle, a lane per column beyond."""
+    fakehip.run(runtime, """
+        for N, nel, planes in ((7, (2, 2, 2), 8), (7, (8, 8, 13), 8), (7, (8, 8, 14), 1), (3, (8, 16, 16), 4),
+                               (3, (8, 16, 17), 1), (12, (4, 4, 13), 13), (12, (4, 4, 14), 1)):
+            m, info = mesh(N, nel)
+            r, z = np.zeros(info.n_local), np.zeros(info.n_local)
+            L.check(lib.sem_set_schwarz(m, 1, None), "schwarz")
+            fake.fake_clear()
+            L.check(lib.sem_precond_apply(m, r.ctypes.data, z.ctypes.data, None), "precond")
+            (i,) = launches("assemble_kernel")
+            per = max(1, 256 // (N + 1) ** 2)
+            got = fake.fake_grid(i), fake.fake_grid_y(i)
+            assert got == (-(-info.E // per), planes), (N, nel, got)
+            lib.sem_free(m)
+        """)
