@@ -211,10 +211,12 @@ static OperatorEpw default_epw(int N, int64_t E)
     // CG N=12 1000 182: 150.  At three of them, one workgroup of three each:
     // 729 elements N=8 plain 14.0: 12.9, Helmholtz 14.1: 13.2, FP32 9.8: 9.6;
     // N=11 plain 28.3: 25.5, Helmholtz 35.4: 25.7; N=12 plain 37.9: 36.9
-    // (Helmholtz 39.4 against 40.2); N=8 plain 343 elements 12.8: 12.4
+    // (Helmholtz 39.4 against 40.2); CG N=8 54.8: 53.9, N=11 120: 103, N=12 133.5:
+    // 131.7; N=8 plain 343 elements 12.8: 12.4
     if (N >= 8 && E <= 1024) {
         o.cg = o.plain = o.helm = o.plain32 = 1;
         const bool three = E > 512 && E <= 768;
+        if (three && (N == 8 || N >= 11)) o.cg = 3;
         if (three && (N == 8 || N == 11)) o.plain = o.helm = 3;
         if (three && N == 8) o.plain32 = 3;
         if (three && N == 12) o.plain = 3;

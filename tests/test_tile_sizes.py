@@ -25,6 +25,8 @@ CASES = [
     (8, (6, 6, 7), "plain", 1), (8, (7, 7, 7), "plain", 3), (8, (9, 9, 9), "plain", 3), (8, (8, 10, 10), "plain", 1),
     (8, (8, 8, 8), "helm", 1), (8, (9, 9, 9), "helm", 3), (8, (9, 9, 9), "plain32", 3),
     (11, (8, 8, 8), "helm", 1), (11, (9, 9, 9), "helm", 3), (11, (9, 9, 9), "plain", 3),
+    (8, (9, 9, 9), "cg", 3), (11, (9, 9, 9), "cg", 3), (11, (8, 8, 8), "cg", 1), (11, (8, 10, 10), "cg", 1),
+    (12, (9, 9, 9), "cg", 3), (10, (9, 9, 9), "cg", 1),
     (12, (9, 9, 9), "plain", 3), (12, (9, 9, 9), "helm", 1),
 ]
 
