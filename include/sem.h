@@ -356,15 +356,15 @@ void sem_solve_opts_default(sem_solve_opts *opts);
  * from x (at most 3 times).
  * On a small mesh (Jacobi, Poisson operator, no periodic axis of one element,
  * orders 3..10, all elements fit on the device's compute units at once: up to
- * about 10^6 points) the iterations run in one launch whose workgroups keep
- * their elements on chip and exchange face values and partial sums; the copies
- * of a node are summed as sem_gs sums them, poll_every and use_graph do not
- * matter, and the dot products differ from the general iteration's (profile =
- * 1) at rounding level.  It takes one more E-vector of device memory, and the
- * general iteration runs where there is none left.  Solves of other threads
- * that do not fit beside it wait for it.  If other work keeps its workgroups
- * from running together for 20 ms, the general iteration takes over from the
- * same state.
+ * about 10^6 points), a solve of four iterations or more runs them in one
+ * launch whose workgroups keep their elements on chip and exchange face values
+ * and partial sums; the copies of a node are summed as sem_gs sums them,
+ * poll_every and use_graph do not matter, and the dot products differ from the
+ * general iteration's (profile = 1) at rounding level.  It takes one more
+ * E-vector of device memory, and the general iteration runs where there is none
+ * left.  Solves of other threads that do not fit beside it wait for it.  If
+ * other work keeps its workgroups from running together for 20 ms, the general
+ * iteration takes over from the same state.
  * SEM_PREC_MIXED: defect correction -- r = b - A x in FP64, an FP32 PCG solves
  * A d = r/||r|| to inner_tol, x += ||r|| d in FP64, until the FP64 true
  * residual meets tol.  Needs SEM_WITH_FP32.

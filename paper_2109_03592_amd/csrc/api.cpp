@@ -842,6 +842,13 @@ struct ResidentSeat {
     ResidentSeat &operator=(const ResidentSeat &) = delete;
 };
 
+// a solve of fewer iterations keeps to the general iteration: setting a run up
+// and reading its verdict costs some 25 us more than a launch.  fixed_iters 1,
+// 2, 3, 4, us general and resident: 64 elements of order 5 111 and 136, 137 and
+// 142, 158 and 151, 187 and 160; 8 of order 3 104 and 129, 114 and 135, 128 and
+// 142, 144 and 147 (5: 157 and 151); 1210 of order 9 185 and 237, 259 and 287,
+// 333 and 343, 412 and 399
+constexpr int kResidentMinIters = 4;
 // longest wait of a resident run's workgroups for each other, in ticks of the
 // device's 100 MHz clock (20 ms)
 constexpr uint64_t kResidentWait = 2000000;
@@ -930,7 +937,9 @@ struct ResidentCg {
     ResidentShape sh;
     int cus = 0;
     bool on;
-    ResidentCg(const sem_mesh *m, bool profile) : on(!profile && resident_for<T>(m, sh, cus)) {}
+    // limit: iterations the solve may take
+    ResidentCg(const sem_mesh *m, bool profile, int limit)
+        : on(!profile && limit >= kResidentMinIters && resident_for<T>(m, sh, cus)) {}
     bool run(sem_mesh *m, int k, PcgState &hs, hipStream_t s)
     {
         on = on && run_resident<T>(m, sh, cus, k, hs, s);
@@ -966,7 +975,7 @@ static sem_status solve_fp64(sem_mesh *m, const double *b, double *x, const sem_
     if (o.x0_given) SEM_HIP(hipMemcpyAsync(m->x64, x, sizeof(double) * nL, hipMemcpyDeviceToDevice, s));
     else SEM_HIP(hipMemsetAsync(m->x64, 0, sizeof(double) * nL, s));
     const int poll = std::max(1, o.poll_every);
-    ResidentCg<double> resident(m, o.profile != 0);
+    ResidentCg<double> resident(m, o.profile != 0, o.fixed_iters > 0 ? o.fixed_iters : o.max_iter);
 
     if (o.fixed_iters > 0) {
         // throughput mode: exactly fixed_iters iterations from the current x
@@ -1074,7 +1083,7 @@ static sem_status solve_mixed(sem_mesh *m, const double *b, double *x, const sem
     else SEM_HIP(hipMemsetAsync(m->x64, 0, sizeof(double) * nL, s));
     const int poll = std::max(1, o.poll_every);
     const int inner_max = o.inner_max_iter > 0 ? o.inner_max_iter : o.max_iter;
-    ResidentCg<float> resident(m, o.profile != 0);
+    ResidentCg<float> resident(m, o.profile != 0, std::min(inner_max, o.max_iter));
     sem_status status = SEM_OK;
     int total = 0, outer = 0;
     double rel = 0.0;

@@ -26,8 +26,8 @@ def test_called_off_run_changes_nothing(semlib, N, nel):
     m = semlib.box_mesh(N, nel, vertices=SI.jittered_box_vertices(nel, seed=N), with_fp32=True)
     b = m.scatter(torch.from_numpy(SI.uniform_global_values(m.n_global, 3)).cuda())
     guess = m.scatter(torch.from_numpy(SI.uniform_global_values(m.n_global, 4)).cuda())
-    solves = [dict(fixed_iters=1), dict(fixed_iters=40), dict(tol=1e-10, max_iter=20000),
-              dict(tol=1e-10, max_iter=20000, precision="mixed"), dict(tol=1e-10, max_iter=3, raise_on_error=False),
+    solves = [dict(fixed_iters=4), dict(fixed_iters=40), dict(tol=1e-10, max_iter=20000),
+              dict(tol=1e-10, max_iter=20000, precision="mixed"), dict(tol=1e-10, max_iter=5, raise_on_error=False),
               dict(tol=1e-10, max_iter=20000, use_graph=False, poll_every=5)]
     m.set_resident(False)
     assert not m.resident_info()["in_use"]

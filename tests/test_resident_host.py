@@ -30,6 +30,20 @@ def test_iterations_of_a_launch(runtime):
         """)
 
 
+def test_short_solves_take_the_general_iteration(runtime):
+    """Below four iterations a run costs more than it saves."""
+    fakehip.run(runtime, """
+        fake.fake_set_verdict(1)
+        m, info = mesh(5, (3, 3, 3))
+        b, x = np.ones(info.n_local), np.zeros(info.n_local)
+        for steps, runs in ((1, 0), (3, 0), (4, 1), (5, 1)):
+            o = opts(fixed_iters=steps, use_graph=0)
+            fake.fake_clear()
+            L.check(lib.sem_pcg_solve(m, b.ctypes.data, x.ctypes.data, C.byref(o), None, None), "solve")
+            assert len(launches("resident_kernel")) == runs, steps
+        """)
+
+
 def test_runs_in_flight_fit_every_xcd(runtime):
     """The workgroups of a launch go to the 8 XCDs in turn, 32 compute units
     each: 129 and 127 workgroups fit the device's 256 but put 17 + 16 on one
@@ -42,7 +56,7 @@ def test_runs_in_flight_fit_every_xcd(runtime):
             ms = [mesh(3, nel) for nel in sizes]
             def work(m, info):
                 b, x = np.ones(info.n_local), np.zeros(info.n_local)
-                o = opts(fixed_iters=1)
+                o = opts(fixed_iters=4)
                 L.check(lib.sem_pcg_solve(m, b.ctypes.data, x.ctypes.data, C.byref(o), None, None), "solve")
             fake.fake_clear()
             th = [threading.Thread(target=work, args=m) for m in ms]
