@@ -72,10 +72,20 @@ struct Group {
     int coarse_steps = 0;  // most Chebyshev steps of a slot with the coarse term (0: none has it)
     unsigned orders = 0;          // orders present in the tables
     int prec = 0;                 // precision of the operator launches (tile sizes follow it)
-    hipGraphExec_t graph = nullptr;
-    int graph_k = 0;
-    unsigned graph_orders = 0;    // orders the cached graph launches
-    int graph_steps = 0;          // coarse launches the cached graph holds
+    // captured iterations: the operators of the orders in turn, side by side
+    struct Graph {
+        hipGraphExec_t exec = nullptr;
+        int k = 0;            // iterations
+        unsigned orders = 0;  // orders it launches
+        int steps = 0;        // coarse launches it holds
+    } graphs[2];
+    void drop_graphs()
+    {
+        for (Graph &c : graphs) {
+            if (c.exec) (void)hipGraphExecDestroy(c.exec);
+            c.exec = nullptr;
+        }
+    }
     GroupDev dev() const
     {
         GroupDev g;
@@ -212,10 +222,7 @@ static void group_reserve(sem_batch *B, Group &g, int64_t nax, int64_t ngs, int6
         g.cap_cv = c;
         grown = true;
     }
-    if (grown && g.graph) {
-        hipGraphExecDestroy(g.graph);
-        g.graph = nullptr;
-    }
+    if (grown) g.drop_graphs();
 }
 
 // rebuild a group's tables for the given slots and upload them on stream s
@@ -326,16 +333,29 @@ static void group_coarse(sem_batch *B, const Group &g, int prec, bool at_start, 
     if (steps > 0) SEM_HIP(batch_coarse(prec, at_start, steps, B->d_desc, B->d_cdesc, g.dev(), launch_for(B, g), s));
 }
 
-// The operators of the group's orders; in a captured FP64 iteration side by
-// side, as a few hundred elements of one order leave most of the device idle
-// (12 boxes of up to 1024 elements, us per iteration: 11 + 27 + 37 in turn, the
-// whole solve 51.3 -> 48.9 ms; boxes of up to 64 and 256 elements 13.4 -> 13.4
-// and 18.3 -> 17.3 ms).  FP32 operators are little longer than the join: mixed
-// solves of these batches took 50.9 -> 52.3, 16.8 -> 17.8 and 23.3 -> 24.4 ms
-// side by side, and stay in turn.
-static void enqueue_ax(sem_batch *B, int prec, const GroupDev &gd, const BatchLaunch &L, hipStream_t s)
+// Whether a captured FP64 iteration launches the operators of the group's
+// orders side by side: a few hundred elements of one order leave most of the
+// device idle, but the fork and the join cost an iteration some 20 us more than
+// launches in turn.  From three orders of 5 and more on (launches of 9 to 20 us
+// and longer) what runs beside the longest pays for that: whole solves over
+// those in turn, orders 5, 7, 9 with 8 elements each 1.01, with 64 0.96, with
+// 512 0.95 and 0.97, 4 to 7 0.86 to 0.98, 8 to 10 0.80 to 0.98, 12 boxes of
+// mixed sizes up to 1024 elements 0.92.  Two orders lost 2 to 25% and orders 2,
+// 3, 4 (launches of 5 to 12 us) 6 to 31%; a group comes down to fewer orders as
+// its slots converge, so the choice is made for each step.  FP32 operators are
+// little longer than the join and stay in turn (mixed solves 2 to 5% slower
+// side by side).
+static bool side_by_side(const Group &g, int prec)
 {
-    if (prec != 0 || !B->capture || s != B->capture || (L.orders & (L.orders - 1)) == 0) {
+    int n = 0;
+    for (int N = 5; N <= SEM_MAX_ORDER; ++N) n += (g.orders >> N) & 1;
+    return prec == 0 && n >= 3;
+}
+
+// the operators of the group's orders, in turn or (under capture) side by side
+static void enqueue_ax(sem_batch *B, int prec, const GroupDev &gd, const BatchLaunch &L, bool side, hipStream_t s)
+{
+    if (!side) {
         SEM_HIP(batch_ax(prec, 2, B->d_desc, gd, L, s));
         return;
     }
@@ -350,9 +370,9 @@ static void enqueue_ax(sem_batch *B, int prec, const GroupDev &gd, const BatchLa
             SEM_HIP(batch_ax(prec, 2, B->d_desc, gd, one, s));
             continue;
         }
-        hipStream_t side = B->side[lane - 1];
-        SEM_HIP(hipStreamWaitEvent(side, B->fork, 0));
-        SEM_HIP(batch_ax(prec, 2, B->d_desc, gd, one, side));
+        hipStream_t other = B->side[lane - 1];
+        SEM_HIP(hipStreamWaitEvent(other, B->fork, 0));
+        SEM_HIP(batch_ax(prec, 2, B->d_desc, gd, one, other));
     }
     for (int i = 0; i < 2 && i + 1 < q; ++i) {
         SEM_HIP(hipEventRecord(B->join[i], B->side[i]));
@@ -361,12 +381,13 @@ static void enqueue_ax(sem_batch *B, int prec, const GroupDev &gd, const BatchLa
 }
 
 // one CG iteration of every slot in g, precision prec
-static void enqueue_batch_iters(sem_batch *B, Group &g, int prec, int k, unsigned orders, int steps, hipStream_t s)
+static void enqueue_batch_iters(sem_batch *B, Group &g, int prec, int k, unsigned orders, int steps, bool side,
+                                hipStream_t s)
 {
     const GroupDev gd = g.dev();
     const BatchLaunch L = launch_for(B, orders, g.prec);
     for (int it = 0; it < k; ++it) {
-        enqueue_ax(B, prec, gd, L, s);
+        enqueue_ax(B, prec, gd, L, side, s);
         SEM_HIP(batch_gs(prec, 1, B->d_desc, gd, L, s));
         SEM_HIP(batch_reduce_sigma(prec, B->d_desc, gd, L, s));
         SEM_HIP(batch_update(prec, B->d_desc, gd, L, s));
@@ -379,18 +400,19 @@ static void run_batch_iters(sem_batch *B, Group &g, int prec, int k, bool use_gr
 {
     if (g.h_slots.empty()) return;
     if (!use_graph) {
-        enqueue_batch_iters(B, g, prec, k, g.orders, g.coarse_steps, s);
+        enqueue_batch_iters(B, g, prec, k, g.orders, g.coarse_steps, false, s);
         return;
     }
     // a cached graph serves any membership whose orders and coarse phases it
     // launches (an order or a phase without items exits at once)
-    if (!g.graph || g.graph_k != k || (g.orders & ~g.graph_orders) != 0 ||
-        g.coarse_steps > g.graph_steps) {
-        const unsigned orders = g.orders | (g.graph ? g.graph_orders : 0u);
-        const int steps = std::max(g.coarse_steps, g.graph ? g.graph_steps : 0);
-        if (g.graph) {
-            SEM_HIP(hipGraphExecDestroy(g.graph));
-            g.graph = nullptr;
+    const bool side = side_by_side(g, prec);
+    Group::Graph &c = g.graphs[side ? 1 : 0];
+    if (!c.exec || c.k != k || (g.orders & ~c.orders) != 0 || g.coarse_steps > c.steps) {
+        const unsigned orders = g.orders | (c.exec ? c.orders : 0u);
+        const int steps = std::max(g.coarse_steps, c.exec ? c.steps : 0);
+        if (c.exec) {
+            SEM_HIP(hipGraphExecDestroy(c.exec));
+            c.exec = nullptr;
         }
         for (hipStream_t *q : {&B->capture, &B->side[0], &B->side[1]})
             if (!*q) SEM_HIP(hipStreamCreateWithFlags(q, hipStreamNonBlocking));
@@ -399,7 +421,7 @@ static void run_batch_iters(sem_batch *B, Group &g, int prec, int k, bool use_gr
         hipGraph_t gr = nullptr;
         SEM_HIP(hipStreamBeginCapture(B->capture, hipStreamCaptureModeThreadLocal));
         try {
-            enqueue_batch_iters(B, g, prec, k, orders, steps, B->capture);
+            enqueue_batch_iters(B, g, prec, k, orders, steps, side, B->capture);
         } catch (...) {
             hipStreamEndCapture(B->capture, &gr);
             if (gr) hipGraphDestroy(gr);
@@ -410,12 +432,12 @@ static void run_batch_iters(sem_batch *B, Group &g, int prec, int k, bool use_gr
         const hipError_t e = hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0);
         hipGraphDestroy(gr);
         SEM_HIP(e);
-        g.graph = ex;
-        g.graph_k = k;
-        g.graph_orders = orders;
-        g.graph_steps = steps;
+        c.exec = ex;
+        c.k = k;
+        c.orders = orders;
+        c.steps = steps;
     }
-    SEM_HIP(hipGraphLaunch(g.graph, s));
+    SEM_HIP(hipGraphLaunch(c.exec, s));
 }
 
 static void read_states(sem_batch *B, hipStream_t s)
@@ -855,7 +877,7 @@ sem_status sem_batch_free(sem_batch *B)
 {
     if (!B) return SEM_OK;
     for (Group *g : {&B->g64, &B->g32, &B->gres})
-        if (g->graph) hipGraphExecDestroy(g->graph);
+        g->drop_graphs();
     if (B->capture) hipStreamDestroy(B->capture);
     for (hipStream_t q : B->side)
         if (q) hipStreamDestroy(q);
@@ -1061,10 +1083,7 @@ sem_status sem_batch_tune(sem_batch *B, sem_mesh *const *meshes, int n, void *st
             // (the persistent grid stays at its default: a grid tuned on one
             // precision's launches underfills the GPU for the other's)
             for (Group *g : {&B->g64, &B->g32})
-                if (g->graph) {
-                    hipGraphExecDestroy(g->graph);
-                    g->graph = nullptr;
-                }
+                g->drop_graphs();
         } catch (...) {
             cleanup();
             throw;
@@ -1086,10 +1105,7 @@ sem_status sem_batch_set_epw(sem_batch *B, int N, int epw)
         B->epw[0][N] = epw;
         B->epw[1][N] = epw;
         for (Group *g : {&B->g64, &B->g32})
-            if (g->graph) {
-                hipGraphExecDestroy(g->graph);
-                g->graph = nullptr;
-            }
+            g->drop_graphs();
         return SEM_OK;
     });
 }
@@ -1104,10 +1120,7 @@ sem_status sem_batch_set_grid(sem_batch *B, int ax_grid, int vec_grid)
         B->L.ax_grid = ax_grid > 0 ? ax_grid : cap;
         B->L.vec_grid = vec_grid > 0 ? vec_grid : cap;
         for (Group *g : {&B->g64, &B->g32, &B->gres})
-            if (g->graph) {
-                hipGraphExecDestroy(g->graph);
-                g->graph = nullptr;
-            }
+            g->drop_graphs();
         return SEM_OK;
     });
 }

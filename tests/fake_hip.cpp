@@ -23,6 +23,7 @@ struct Launch {
     size_t lds;
     int iters;        // resident runs
     bool has_scratch;
+    hipStream_t stream;
 };
 std::map<const void *, std::string> names;
 std::set<void *> blocks;
@@ -72,6 +73,7 @@ const char *fake_name(int i) { return launches[i].name.c_str(); }
 unsigned fake_grid(int i) { return launches[i].grid; }
 unsigned fake_grid_y(int i) { return launches[i].grid_y; }
 unsigned fake_block(int i) { return launches[i].block; }
+int64_t fake_stream(int i) { return (int64_t)launches[i].stream; }
 int fake_iters(int i) { return launches[i].iters; }
 int fake_has_scratch(int i) { return launches[i].has_scratch; }
 
@@ -108,10 +110,10 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
     *s = cfg_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, hipStream_t)
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, hipStream_t s)
 {
     std::unique_lock<std::mutex> lock(mu);
-    Launch l{names[f], g.x, g.y, b.x, lds, 0, false};
+    Launch l{names[f], g.x, g.y, b.x, lds, 0, false, s};
     if (l.name.find("resident_kernel") != std::string::npos) {
         if (hold_ms) {  // the run takes its time
             max_in_flight = std::max(max_in_flight, ++in_flight);
@@ -215,8 +217,9 @@ const char *hipGetErrorString(hipError_t) { return "error"; }
 
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned)
 {
-    static int one;
-    *s = reinterpret_cast<hipStream_t>(&one);
+    static char many[1024];
+    static int next = 0;
+    *s = reinterpret_cast<hipStream_t>(many + next++ % 1024);
     return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }

@@ -17,7 +17,8 @@ import sys
 sys.path.insert(0, {tests!r})
 fake = C.CDLL({so!r}, mode=C.RTLD_GLOBAL)
 fake.fake_name.restype = C.c_char_p
-fake.fake_allocated.restype = fake.fake_copied.restype = C.c_int64
+fake.fake_allocated.restype = fake.fake_copied.restype = fake.fake_stream.restype = C.c_int64
+fake.fake_fill.argtypes = [C.c_double]
 spec = importlib.util.spec_from_file_location("semlib_c", {lib!r})
 L = importlib.util.module_from_spec(spec)
 spec.loader.exec_module(L)

@@ -23,7 +23,6 @@ def test_set_up_sends_the_rows_alone(tmp_path):
     """Per element its 64 block entries and 8 corners, per vertex its row and
     its inverse diagonal, and the order's small tables."""
     fakehip.run(fakehip.build(tmp_path), """
-        fake.fake_fill.argtypes = [C.c_double]
         for nel, k in (((6, 5, 4), 4), ((16, 16, 16), 4), ((24, 24, 20), 9)):
             m, info = mesh(2, nel)
             nvert = (nel[0] + 1) * (nel[1] + 1) * (nel[2] + 1)
